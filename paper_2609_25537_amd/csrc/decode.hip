@@ -191,7 +191,6 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // the last-level cache (ordinary / V non-temporal / K and V / K only):
 // 74.7 / 66.1 / 66.7 / 70.1 us; the 32-layer stack 38.4 / 36.3 / 36.3 /
 // 36.7 us; the Dh = 256 layer 136.5 / 128.4 / 139.6 / 127.8 us.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <bool NT = false>
 __device__ __forceinline__ uint4 ld16(const void *p) {
     if constexpr (NT) {

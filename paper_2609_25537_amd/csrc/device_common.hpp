@@ -38,6 +38,15 @@ template <> struct Vec16<uint16_t> {
     }
 };
 
+// 16-byte store marked non-temporal.  An ordinary store leaves its line dirty
+// in the XCD's L2, and the kernel does not end before those lines have been
+// written back: 512 workgroups writing 4 KB each took 18 us with ordinary
+// stores and 3.2 us with these.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void st16_nt(void *p, const uint4 &v) {
+    __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(p));
+}
+
 // ------------------------------------------------------- lane exchange
 //
 // Exchanging v with lane (lane ^ M): masks 1 and 2 are DPP

@@ -174,6 +174,32 @@ def test_window_append_ring(orc, dtype, Dh, W, T):
     assert (to_host(dc) == cnt).all()
 
 
+@pytest.mark.parametrize("dtype,Dh,Hkv,W,T", [
+    # 16-byte vectors per sequence around the sizes where another kernel takes
+    # over: 1024 (one workgroup of 256 threads, then of 1024) and 8192 (then
+    # the whole chip, whose last run of 1024 vectors per head is partial)
+    ("bf16", 128, 2, 40, 32), ("bf16", 128, 2, 40, 33), ("bf16", 128, 2, 300, 256), ("bf16", 128, 2, 300, 257),
+    ("f32", 256, 3, 130, 130), ("bf16", 64, 1, 2000, 1999), ("f32", 64, 5, 1024, 1024),
+])
+def test_window_append_many_rows(orc, dtype, Dh, Hkv, W, T):
+    """Prefill-sized appends, twice (so that both wrap), bit-exact."""
+    rng = np.random.default_rng(W + T)
+    B = 3
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    mk = (lambda *s: _bf16(f(*s))) if dtype == "bf16" else f
+    wk, wv = mk(B, Hkv, W, Dh), mk(B, Hkv, W, Dh)
+    cnt = np.array([0, W - 1, 5 * W + 3], np.int32)
+    dk, dv, dc = to_dev(wk), to_dev(wv), to_dev(cnt)
+    for step in range(2):
+        say(f"append {dtype} Dh={Dh} Hkv={Hkv} W={W} T={T} step {step}")
+        nk, nv = mk(B, Hkv, T, Dh), mk(B, Hkv, T, Dh)
+        orc.window_append(wk, wv, cnt, nk, nv)
+        cmc.cmc_window_append(dk, dv, dc, to_dev(nk), to_dev(nv))
+        torch.cuda.synchronize()
+        assert (to_host(dk) == wk).all() and (to_host(dv) == wv).all()
+        assert (to_host(dc) == cnt).all()
+
+
 # ------------------------------------------------------------------ gather
 
 @pytest.mark.parametrize("dtype,Dh,idx_mode,k_len", [
