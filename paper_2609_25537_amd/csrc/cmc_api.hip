@@ -64,27 +64,33 @@ cmc_status check_keys(const char *fn, cmc_dtype key_dtype, int D) {
 #ifndef CMC_DECODE_GRANULE
 #define CMC_DECODE_GRANULE 64
 #endif
-// Build-time tuning knob: fewest (sequence, kv head) pairs that take one
-// 8-wave workgroup each (up to 256 pairs).
-#ifndef CMC_DECODE_WIDE_MIN_PAIRS
-#define CMC_DECODE_WIDE_MIN_PAIRS 192
-#endif
-
 namespace cmc {
 
 // Key-axis split plan.  The decode kernel keeps eight waves resident per CU
-// (two per SIMD), so about 2048 waves fill the 256 CUs in one round.
-//   - With 192..256 (sequence, kv head) pairs, each pair gets one 8-wave
-//     workgroup (S = 1): one round and no cross-workgroup merge.
-//   - Otherwise workgroups have 4 waves, two resident per CU, and the plan
-//     aims for about kTargetWG of them: a pair is split only when there are
-//     fewer pairs than that, never below kGranule keys per split.
-// The plan depends only on sizes, so the workspace query and the launch
-// always agree.
-DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W) {
+// (two per SIMD), so about 2048 waves, 512 workgroups of 4, fill the 256 CUs
+// in one round; what the rules below avoid is a second round that is mostly
+// empty, and splits whose partials and merge cost more than they spread.
+// Launch times in us before / after, Hkv = 8 and 256 + 512 keys, G = 4, Dh =
+// 128 in bf16 unless said otherwise:
+//   - From 129 (sequence, kv head) pairs (168 with Dh = 64) to 256, one 8-wave
+//     workgroup each, no merge, instead of 4-wave splits: 136 pairs 21.8 /
+//     18.5, 184 pairs 26.7 / 18.7 (512 + 1024 keys: 30.1 / 29.0, 35.8 / 29.0;
+//     G = 8: 23.0 / 22.1, 26.6 / 22.7).  Dh = 64 moves half the bytes per key
+//     and only gains from 168 on: at 136 pairs 13.2 / 13.6, at 168 15.9 / 13.6.
+//   - Otherwise 4-wave workgroups, a pair cut into as many splits as fit one
+//     round, the appended rows' own split counted: 40 pairs 13.4 / 12.4, 96
+//     pairs 19.2 / 14.5, 128 pairs 21.4 / 16.4.  (Rounding up instead, and the
+//     appended rows' splits on top, made 640 workgroups of 128 pairs.)
+//   - From 257 to 367 pairs that leaves one workgroup per pair and up to half
+//     of the chip's slots empty, so the pairs are cut in two after all (264
+//     pairs of 512 + 1024 keys: 51.5 cut, 55.5 not; fp32, Dh = 64: 52 / 60);
+//     from 368 on one workgroup per pair is faster (384 pairs: 37.7 cut, 31.6
+//     not; 448 pairs 43.1 / 33.5).  The same from 129 to 167 pairs with Dh =
+//     64 (fp32 G = 1, 136 pairs: 27.5 cut in four, 31.6 cut in two).
+// Never below kGranule keys per split.
+DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W, bool append) {
     constexpr long long kTargetWG = CMC_DECODE_TARGET_WG;
     constexpr long long kGranule = CMC_DECODE_GRANULE;
-    constexpr long long kWideMinPairs = CMC_DECODE_WIDE_MIN_PAIRS;
     // The merge stages S*G*2 floats in the kernel's LDS; one split more is
     // reserved for appended rows.
     constexpr long long kMaxSplits = 127;
@@ -92,26 +98,30 @@ DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W) {
     const long long L = (long long)k + W;
     const long long pairs = (long long)B * Hkv;
     if (L <= 0 || pairs <= 0) return pl;
+    append = append && W > 0;
+    const int G = Hq / Hkv;
+    const long long wide_min = Dh >= 128 ? 129 : 168;
     long long S, chunk;
-    if (pairs >= kWideMinPairs && pairs <= 256 && decode_waves_ok(8, Hq / Hkv, Dh)) {
+    if (pairs >= wide_min && pairs <= 256 && decode_waves_ok(8, G, Dh)) {
         pl.waves = 8;
         S = 1;
         chunk = L;
     } else {
-        const long long s_target = std::max(1LL, (kTargetWG + pairs - 1) / pairs);
+        const bool round_up = (pairs > 256 && pairs < 368) || (Dh == 64 && pairs > 128 && pairs < wide_min);
+        const long long s_target = round_up ? (kTargetWG + pairs - 1) / pairs
+                                            : std::max(1LL, kTargetWG / pairs - (append ? 1 : 0));
         chunk = (L + s_target - 1) / s_target;
         chunk = std::max(chunk, (L + kMaxSplits - 1) / kMaxSplits);
         chunk = ((chunk + kGranule - 1) / kGranule) * kGranule;
         S = (L + chunk - 1) / chunk;
     }
-    const int G = Hq / Hkv;
     pl.S = (int)S;
     pl.chunk = (int)chunk;
     // A split plan merges partials anyway: the rows appended in a call then
     // get a split of their own, so no workgroup handles ring rows and
     // appended rows one after the other.
-    const long long Sa = S > 1 && W > 0 ? S + 1 : S;
-    pl.S_alloc = (int)Sa;
+    pl.own_append = S > 1 && append;
+    const long long Sa = pl.own_append ? S + 1 : S;
     pl.counter_bytes = align256((size_t)(B + pairs) * sizeof(unsigned));
     pl.ml_bytes = Sa > 1 ? align256((size_t)(pairs * Sa * G * 2) * sizeof(float)) : 0;
     pl.acc_bytes = Sa > 1 ? align256((size_t)(pairs * Sa * G * Dh) * sizeof(float)) : 0;
@@ -391,7 +401,8 @@ cmc_status cmc_gather_tier1(const void *cme_k, const void *cme_v, cmc_dtype kv_d
 
 size_t cmc_decode_workspace_bytes(int B, int Hq, int Hkv, int Dh, int k, int W) {
     if (B < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || k < 0 || W < 0 || !supported_dh(Dh)) return 0;
-    return cmc::plan_decode(B, Hq, Hkv, Dh, k, W).total;
+    return std::max(cmc::plan_decode(B, Hq, Hkv, Dh, k, W, false).total,
+                    cmc::plan_decode(B, Hq, Hkv, Dh, k, W, true).total);
 }
 
 }  // extern "C"
@@ -492,7 +503,7 @@ cmc_status decode_impl(const char *fn, const float *q, const void *cme_k, const 
         misaligned(win_v) || misaligned(win_count) || misaligned(out) || misaligned(workspace) ||
         misaligned(new_k) || misaligned(new_v))
         return fail(CMC_ERR_UNSUPPORTED, "%s: every pointer must be 16-byte aligned", fn);
-    const cmc::DecodePlan pl = cmc::plan_decode(B, Hq, Hkv, Dh, k, W);
+    const cmc::DecodePlan pl = cmc::plan_decode(B, Hq, Hkv, Dh, k, W, T_new > 0);
     char *counters, *partials;
     if (noalloc) {
         const size_t nctr = ((size_t)B + (size_t)B * Hkv) * sizeof(unsigned);
@@ -507,8 +518,9 @@ cmc_status decode_impl(const char *fn, const float *q, const void *cme_k, const 
         counters = base;
         partials = base + kNoAllocCounterBytes;
     } else {
-        if (!workspace || workspace_bytes < pl.total)
-            return fail(CMC_ERR_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, pl.total,
+        const size_t need = cmc_decode_workspace_bytes(B, Hq, Hkv, Dh, k, W);
+        if (!workspace || workspace_bytes < need)
+            return fail(CMC_ERR_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, need,
                         workspace ? workspace_bytes : (size_t)0);
         counters = static_cast<char *>(workspace);
         partials = counters + pl.counter_bytes;
@@ -536,7 +548,7 @@ cmc_status decode_impl(const char *fn, const float *q, const void *cme_k, const 
     p.Hkv = Hkv;
     p.N = N;
     p.T_new = T_new;
-    p.new_split = (pl.S > 1 && T_new > 0) ? 1 : 0;
+    p.new_split = pl.own_append ? 1 : 0;
     p.S = pl.S + p.new_split;
     p.chunk = pl.chunk;
     p.waves = pl.waves;

@@ -15,21 +15,25 @@
 // after every workgroup of the sequence has read it.  The result equals
 // cmc_window_append followed by the decode.
 //
-// Main loop, two variants:
-//   MFMA (bf16 K/V, G <= 4): a wave takes 16 keys per block.  S = Q K^T is one
-//     v_mfma_f32_16x16x32_bf16 chain per Dh/32 slice, with the 16 A-rows
-//     holding the G query heads repeated (row m = head m % G), so every lane
-//     ends with all G scores of key (lane % 16).  q is split into bf16
-//     hi + lo parts (two MFMAs per slice), which keeps the logit error at the
-//     level of fp32 accumulation.  P V runs on the VALU in fp32 in four
-//     quarters of 4 keys: lane l owns key (l & 3) of each quarter and Dh/16
-//     dims; the p values reach that layout through 16 x G floats of LDS
-//     private to the wave.  V rows are loaded non-temporally, K rows with
-//     ordinary loads (see ld16).
-//   VALU (fp32 K/V, or G = 8): 16-byte lane loads, LPR lanes per row, dot
-//     products reduced by a DPP butterfly.
-// Both keep an online softmax per wave (running max in log2 units, q
-// pre-scaled by scale*log2 e), then combine the waves through LDS.
+// Main loop: a wave takes 16 keys per block.  S = Q K^T on MFMA, the 16
+// A-rows holding the G query heads repeated (row m = head m % G), so every lane
+// ends with the scores of key (lane % 16) for all heads (G <= 4) or for four
+// of the eight (G = 8: heads 4 ((lane / 16) % 2) .. + 3).
+//   bf16 K/V: one v_mfma_f32_16x16x32_bf16 chain per Dh/32 slice, q split into
+//     bf16 parts (hi + lo, two MFMAs per slice, for G <= 4; three parts, the
+//     whole fp32 significand, for G = 8), which keeps the logit error at the
+//     level of fp32 accumulation.
+//   fp32 K/V: v_mfma_f32_16x16x4_f32, fp32 products and sums throughout.
+// P V runs on the VALU in fp32 in four quarters of 4 keys: lane l owns key
+// (l & 3) of each quarter and Dh/16 dims; the p values reach that layout
+// through 16 x G floats of LDS private to the wave.  V rows are loaded
+// non-temporally, K rows with ordinary loads (see ld16).  Each wave keeps an
+// online softmax (running max in log2 units, q pre-scaled by scale*log2 e),
+// then the waves are combined through LDS.
+// Measured, with this loop in place of one that loaded 4 - 16 rows at a time
+// and reduced their dot products across lanes, waiting for each load: 24
+// ragged sequences of 64/8 heads (bf16, Dh = 128, G = 8) 155 -> 36 us; fp32, 30
+// sequences of 32/8 heads, Dh = 128, 1000 keys 74.6 -> 48.8 us.
 //
 // Latency (one launch of a single layer at batch 1 is a chain of memory round
 // trips, not a stream): the first K/V loads depend only on kernel arguments
@@ -50,6 +54,8 @@
 // list is empty gets zeros.
 #include <limits.h>
 
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -57,122 +63,16 @@ namespace cmc {
 
 namespace {
 
-// Build-time tuning knob: smallest query-group size that takes the MFMA path
-// (smaller groups use the VALU path).
-#ifndef CMC_MFMA_MIN_G
-#define CMC_MFMA_MIN_G 1
-#endif
-// Build-time tuning knob: widest head that double-buffers its K/V rows.
-#ifndef CMC_DOUBLE_BUFFER_MAX_DH
-#define CMC_DOUBLE_BUFFER_MAX_DH 128
+// Build-time tuning knob: widest K/V row, in bytes, that is double-buffered
+// (wider rows' second register set would cost a wave per SIMD).
+#ifndef CMC_DOUBLE_BUFFER_MAX_ROW
+#define CMC_DOUBLE_BUFFER_MAX_ROW 256
 #endif
 
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// K/V row pointers of one key; rk/rv are set (to the ring slot the row must
-// be written to) only for a row appended in this call.
-template <typename T>
-struct RowPtrs {
-    const T *k, *v;
-    T *rk, *rv;
-};
-
-// Where the rows of sequence b's key list live, for one kv head (the
-// layout of the MFMA path's phases, below): rows [0, k) are pool rows
-// idx[row] (clamped into the pool), rows [k, k + W) ring slots row - k
-// (masked as in RingRows), rows [k + W, k + W + T_new) the appended rows,
-// written to ring slots (slot0 + t) mod W.
-template <typename T>
-struct RowMap {
-    int stride;               // elements per row (Dh)
-    const T *poolK, *poolV;   // pool of this (b, kv head)
-    T *winK, *winV;           // ring of this (b, kv head)
-    const T *newK, *newV;     // appended rows of this (b, kv head)
-    const int32_t *idx;       // this sequence's index list, or nullptr
-    int k, W, nmax, slot0, T_new, nvalid;
-};
-
-// Row lookup on values already in registers (free functions over scalars:
-// selecting between fields of a struct in memory would keep it on the
-// stack).  fetch_row() issues the only memory access of a lookup -- the
-// index-list entry of a pool row -- so callers can prefetch it one block
-// ahead; row_ptrs() is pure arithmetic on its result.
-__device__ __forceinline__ int fetch_row(int row, const int32_t *idx, int k) {
-    return (row < k && idx) ? idx[row] : row;
-}
-
-template <typename T>
-__device__ __forceinline__ RowPtrs<T> row_ptrs(int row, int r, const T *poolK, const T *poolV, T *winK,
-                                               T *winV, const T *newK, const T *newV, int k, int W, int nmax,
-                                               int slot0, int T_new, int stride) {
-    const bool in_pool = row < k;
-    r = r < 0 ? 0 : (r > nmax ? nmax : r);
-    const int slot = row - k;
-    const bool is_new = !in_pool && slot >= W;
-    const int t = slot - W;  // appended row, when is_new
-    int ws = slot0 + t;      // its ring slot
-    ws -= ws >= W ? W : 0;
-    const size_t op = (size_t)r * stride, ow = (size_t)slot * stride, on = (size_t)t * stride,
-                 oa = (size_t)ws * stride;
-    RowPtrs<T> o;
-    o.k = in_pool ? poolK + op : (is_new ? newK + on : winK + ow);
-    o.v = in_pool ? poolV + op : (is_new ? newV + on : winV + ow);
-    o.rk = is_new ? winK + oa : nullptr;
-    o.rv = is_new ? winV + oa : nullptr;
-    return o;
-}
-
-// Whether key-list row `row` holds a key of this step (only ring slots can
-// be masked).
-__device__ __forceinline__ bool row_valid(int row, int k, int W, int slot0, int T_new, int nvalid) {
-    const int s = row - k;
-    if (s < 0 || s >= W) return true;
-    int d = s - slot0;
-    d += d < 0 ? W : 0;
-    return s < nvalid && d >= T_new;
-}
-
-// Unpacks a RowMap into locals and defines LOCATE(row) over them.
-#define CMC_UNPACK_ROWMAP(rm)                                                            \
-    const auto poolK_ = (rm).poolK;                                                      \
-    const auto poolV_ = (rm).poolV;                                                      \
-    const auto winK_ = (rm).winK;                                                        \
-    const auto winV_ = (rm).winV;                                                        \
-    const auto newK_ = (rm).newK;                                                        \
-    const auto newV_ = (rm).newV;                                                        \
-    const int32_t *idx_ = (rm).idx;                                                      \
-    const int k_ = (rm).k, W_ = (rm).W, nmax_ = (rm).nmax, slot0_ = (rm).slot0,          \
-              tnew_ = (rm).T_new, stride_ = (rm).stride, nvalid_ = (rm).nvalid
-#define FETCH(row) fetch_row(row, idx_, k_)
-#define PTRS(row, r) \
-    row_ptrs(row, r, poolK_, poolV_, winK_, winV_, newK_, newV_, k_, W_, nmax_, slot0_, tnew_, stride_)
-#define LOCATE(row) PTRS(row, FETCH(row))
-#define VALID(row) row_valid(row, k_, W_, slot0_, tnew_, nvalid_)
-
-template <typename T>
-__device__ __forceinline__ RowMap<T> make_rowmap(const DecodeParams &p, int b, int kvh, int DH, int kb,
-                                                 int slot0, int nvalid) {
-    RowMap<T> m;
-    const size_t head = (size_t)b * p.Hkv + kvh;
-    m.poolK = static_cast<const T *>(p.cme_k) + head * (size_t)p.N * DH;
-    m.poolV = static_cast<const T *>(p.cme_v) + head * (size_t)p.N * DH;
-    m.winK = p.W > 0 ? static_cast<T *>(p.win_k) + head * (size_t)p.W * DH : nullptr;
-    m.winV = p.W > 0 ? static_cast<T *>(p.win_v) + head * (size_t)p.W * DH : nullptr;
-    m.newK = p.T_new > 0 ? static_cast<const T *>(p.new_k) + head * (size_t)p.T_new * DH : nullptr;
-    m.newV = p.T_new > 0 ? static_cast<const T *>(p.new_v) + head * (size_t)p.T_new * DH : nullptr;
-    m.idx = p.idx ? p.idx + (size_t)b * p.k : nullptr;
-    m.k = kb;
-    m.W = p.W;
-    m.nmax = p.N > 0 ? p.N - 1 : 0;
-    m.slot0 = slot0;
-    m.T_new = p.T_new;
-    m.nvalid = nvalid;
-    m.stride = DH;
-    return m;
-}
 
 // Orders this wave's LDS writes before its following LDS reads (and reads
 // before later writes).  LDS operations of one wave execute in order, so only
@@ -202,15 +102,21 @@ __device__ __forceinline__ uint4 ld16(const void *p) {
 }
 __device__ __forceinline__ void st16(void *p, const uint4 &v) { *reinterpret_cast<uint4 *>(p) = v; }
 
+// Query heads whose scores one lane holds (C rows per lane of the MFMA tile).
+template <int G>
+constexpr int kLaneHeads = G < 4 ? G : 4;
+
 // Per-wave online-softmax state for G heads and VEC output dims per lane.
+// Every lane holds all G running maxima; the denominators are those of the
+// lane's own heads (all of them for G <= 4).
 template <int G, int VEC>
 struct WaveState {
-    float m[G], l[G], acc[G][VEC];
+    float m[G], l[kLaneHeads<G>], acc[G][VEC];
     __device__ __forceinline__ void init() {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             m[g] = -INFINITY;
-            l[g] = 0.f;
+            if (g < kLaneHeads<G>) l[g] = 0.f;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[g][i] = 0.f;
         }
@@ -314,12 +220,9 @@ struct RingRows {
     __device__ __forceinline__ bool all_valid(int r0, int r1) const {
         const int s0 = r0 - first, s1 = r1 - first;
         if (s1 > nvalid) return false;
-        for (int t = 0; t < T_new; ++t) {
-            int sl = cnt_mod + t;
-            sl -= sl >= W ? W : 0;
-            if (sl >= s0 && sl < s1) return false;
-        }
-        return true;
+        // the overwritten slots are [cnt_mod, cnt_mod + T_new) mod W
+        const int e = cnt_mod + T_new;
+        return !(s0 < e && s1 > cnt_mod) && s0 >= e - W;
     }
 };
 struct NewRows {
@@ -338,60 +241,217 @@ struct NewRows {
     }
 };
 
-// q's A operand: this lane's slice of query head (lane % 16) % G, pre-scaled,
-// as bf16 hi + lo parts.
-template <int DH, int G>
-__device__ __forceinline__ void load_q_operand(const DecodeParams &p, int b, int kvh, bf16x8 (&qa_hi)[DH / 32],
-                                               bf16x8 (&qa_lo)[DH / 32]) {
-    const int lane = threadIdx.x & 63;
-    const int r16 = lane & 15, q4 = lane >> 4;
-    const float *qp = p.q + ((size_t)b * p.Hq + (size_t)kvh * G + (r16 % G)) * DH + 8 * q4;
-#pragma unroll
-    for (int i = 0; i < DH / 32; ++i) {
-        const float4 x0 = *reinterpret_cast<const float4 *>(qp + 32 * i);
-        const float4 x1 = *reinterpret_cast<const float4 *>(qp + 32 * i + 4);
-        const float xs[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float v = xs[e] * p.qscale;
-            const __bf16 h = (__bf16)v;
-            qa_hi[i][e] = h;
-            qa_lo[i][e] = (__bf16)(v - (float)h);
-        }
-    }
-}
+// q's A operand (this lane's dims of query head (lane % 16) % G, pre-scaled),
+// filled by the first phase that has a block for the wave, after that
+// block's K/V loads are issued (both round trips overlap), and the scores of
+// a 16-key block from it.  The lane's K elements of key lane % 16 are the
+// 16-byte chunks 4 i + lane / 16 of the row; the dims of a chunk are the k
+// indices of one MFMA (bf16) or of four (fp32), in the same order for q.
+//
+// Where the operand would take the registers that a second wave per SIMD
+// needs (eight heads of bf16: three parts and 8 DH/16 accumulators per lane;
+// several 256-wide fp32 heads), the wave keeps it in LDS of its own instead
+// and reads it back for every block: 16 bytes per lane and MFMA (bf16) or
+// four MFMAs (fp32), one copy per head.
+template <typename T, int DH, int G>
+constexpr bool kQInLds = sizeof(T) == 2 ? G > 4 : DH > 128 && G > 1;
 
-// q's A operand, filled by the first phase that has a block for the wave,
-// after that block's K/V loads are issued (both round trips overlap).
-template <int DH>
-struct QOperand {
-    bf16x8 hi[DH / 32], lo[DH / 32];
+template <typename T, int DH, int G>
+struct QOperand;
+
+template <int DH, int G>
+struct QOperand<uint16_t, DH, G> {
+    static constexpr int kChunks = DH / 32;
+    static constexpr bool kLds = kQInLds<uint16_t, DH, G>;
+    // bf16 parts of q: hi + lo carry 16 bits of its significand; the third
+    // completes fp32's 24.  (Two parts: output error 2.6e-6 against 64 bits;
+    // three: 2e-7, what an fp32 dot product gives.)
+    static constexpr int kParts = G > 4 ? 3 : 2;
+    static constexpr int kLdsWords = kLds ? kChunks * kParts * 4 * G : 1;  // 16-byte words per wave
+    bf16x8 part[kLds ? 1 : kParts][kLds ? 1 : kChunks];
+    uint4 *lds;
     bool ready;
+    __device__ __forceinline__ void load(const DecodeParams &p, int b, int kvh) {
+        const int lane = threadIdx.x & 63;
+        const int r16 = lane & 15, q4 = lane >> 4;
+        const float *qp = p.q + ((size_t)b * p.Hq + (size_t)kvh * G + (r16 % G)) * DH + 8 * q4;
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) {
+            const float4 x0 = *reinterpret_cast<const float4 *>(qp + 32 * i);
+            const float4 x1 = *reinterpret_cast<const float4 *>(qp + 32 * i + 4);
+            const float xs[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+            bf16x8 h[kParts];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float v = xs[e] * p.qscale;
+#pragma unroll
+                for (int t = 0; t < kParts; ++t) {
+                    h[t][e] = (__bf16)v;
+                    v -= (float)h[t][e];  // exact
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < kParts; ++t) {
+                if constexpr (kLds) {
+                    if (r16 < G) lds[((i * kParts + t) * 4 + q4) * G + r16] = __builtin_bit_cast(uint4, h[t]);
+                } else {
+                    part[t][i] = h[t];
+                }
+            }
+        }
+        if constexpr (kLds) wave_lds_sync();
+    }
+    __device__ __forceinline__ floatx4 scores(const uint4 (&kr)[kChunks]) const {
+        // Three parts: the small ones summed apart, the large ones in runs of
+        // two slices, so that no partial sum is rounded often.
+        floatx4 c = {0.f, 0.f, 0.f, 0.f}, rest = c, sum = c;
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) {
+            const bf16x8 kbf = __builtin_bit_cast(bf16x8, kr[i]);
+#pragma unroll
+            for (int t = 0; t < kParts; ++t) {
+                bf16x8 a;
+                if constexpr (kLds) {
+                    const int lane = threadIdx.x & 63;
+                    a = __builtin_bit_cast(bf16x8, lds[((i * kParts + t) * 4 + lane / 16) * G + lane % G]);
+                } else {
+                    a = part[t][i];
+                }
+                if constexpr (kParts > 2) {
+                    if (t > 0) rest = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, kbf, rest, 0, 0, 0);
+                    else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, kbf, c, 0, 0, 0);
+                } else {
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, kbf, c, 0, 0, 0);
+                }
+            }
+            if constexpr (kParts > 2) {
+                if (i % 2 == 1) {
+                    sum = sum + c;
+                    c = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+        }
+        return kParts > 2 ? sum + rest : c;
+    }
 };
+
+template <int DH, int G>
+struct QOperand<float, DH, G> {
+    static constexpr int kChunks = DH / 16;
+    // One or two heads: the dot products on the VALU, the lane's chunks of
+    // every head in registers.  An fp32 MFMA step takes 32 cycles however few
+    // of its 16 rows are distinct heads: DH/4 of them per block against
+    // G (DH/4 + 6) VALU instructions of 4 cycles.
+    static constexpr bool kDot = G * DH <= 256 && G <= 2;
+    static constexpr bool kLds = !kDot && kQInLds<float, DH, G>;
+    static constexpr int kLdsWords = kLds ? kChunks * 4 * G : 1;  // 16-byte words per wave
+    float4 x[kDot ? G * kChunks : kLds ? 1 : kChunks];
+    uint4 *lds;
+    bool ready;
+    __device__ __forceinline__ void load(const DecodeParams &p, int b, int kvh) {
+        const int lane = threadIdx.x & 63;
+        const int r16 = lane & 15, q4 = lane >> 4;
+        const float *q0 = p.q + ((size_t)b * p.Hq + (size_t)kvh * G) * DH + 4 * q4;
+        constexpr int kRows = kDot ? G : 1;
+#pragma unroll
+        for (int g = 0; g < kRows; ++g) {
+            const float *qp = q0 + (kDot ? g : r16 % G) * DH;
+#pragma unroll
+            for (int i = 0; i < kChunks; ++i) {
+                const float4 t = *reinterpret_cast<const float4 *>(qp + 16 * i);
+                const float4 u = make_float4(t.x * p.qscale, t.y * p.qscale, t.z * p.qscale, t.w * p.qscale);
+                if constexpr (kLds) {
+                    if (r16 < G) lds[(i * 4 + q4) * G + r16] = __builtin_bit_cast(uint4, u);
+                } else {
+                    x[g * kChunks + i] = u;
+                }
+            }
+        }
+        if constexpr (kLds) wave_lds_sync();
+    }
+    __device__ __forceinline__ floatx4 scores(const uint4 (&kr)[kChunks]) const {
+        floatx4 c = {0.f, 0.f, 0.f, 0.f}, c1 = c, c2 = c, c3 = c, sum = c;
+        if constexpr (kDot) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                float d[4] = {0.f, 0.f, 0.f, 0.f};  // short chains: less rounding, more in flight
+#pragma unroll
+                for (int i = 0; i < kChunks; ++i) {
+                    const float4 a = x[g * kChunks + i];
+                    d[0] = fmaf(a.x, __uint_as_float(kr[i].x), d[0]);
+                    d[1] = fmaf(a.y, __uint_as_float(kr[i].y), d[1]);
+                    d[2] = fmaf(a.z, __uint_as_float(kr[i].z), d[2]);
+                    d[3] = fmaf(a.w, __uint_as_float(kr[i].w), d[3]);
+                }
+                c[g] = lane_reduce<OpSum, 16, kWave>((d[0] + d[1]) + (d[2] + d[3]));
+            }
+            return c;
+        }
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) {
+            float4 a;
+            if constexpr (kLds) {
+                const int lane = threadIdx.x & 63;
+                a = __builtin_bit_cast(float4, lds[(i * 4 + lane / 16) * G + lane % G]);
+            } else {
+                a = x[kDot ? 0 : i];
+            }
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, __uint_as_float(kr[i].x), c, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, __uint_as_float(kr[i].y), c1, 0, 0, 0);
+            c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c2, 0, 0, 0);
+            c3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(kr[i].w), c3, 0, 0, 0);
+            // runs of four chunks, so that no partial sum is rounded often (one
+            // run where the registers are short)
+            constexpr int kRun = DH > 128 && G == 4 ? kChunks : 4;
+            if (i % kRun == kRun - 1) {
+                sum = sum + ((c + c1) + (c2 + c3));
+                c = c1 = c2 = c3 = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+        return sum;
+    }
+};
+
+// Byte offsets from a (sequence, kv head)'s pool or ring base: 32 bits for
+// bf16 (the host checks that they suffice), 64 for fp32.
+template <typename T>
+using row_off_t = std::conditional_t<sizeof(T) == 2, uint32_t, size_t>;
 
 // One phase: rows [r0, r1) from bases kbase/vbase (bytes).  A wave takes 16
 // rows per block.  K: the lane's row blk + (lane % 16) in the MFMA B layout
-// (dims 32i + 8*(lane/16) .. +7).  V: four quarters of 4 rows; in quarter qq
-// the lane owns row blk + 4qq + (lane % 4) and dims (DH/16)*(lane/4) ..
-// +DH/16-1, so each lane accumulates DH/16 output dims per head.  The p
-// values travel from the score layout (lane r holds key r's G weights) to
+// (its 16-byte chunks 4i + lane/16).  V: four quarters of 4 rows; in quarter qq
+// the lane owns row blk + 4qq + (lane % 4) and DH/16 dims of it, the 16-byte
+// words lane/4, lane/4 + 16, ... of the row, so that every load takes whole
+// 256-byte runs of four rows (DH/16 consecutive dims, two to four words at a
+// 32- or 64-byte stride, had each load touch every line of the rows and the
+// non-temporal lines fetched again: bf16 Dh = 256 step 133.0 -> 127.2 us, fp32
+// Dh = 256 of 400 pairs 157 -> 110 us), and accumulates those output dims per
+// head.  The p values travel from the score layout (lane r holds key r's G weights) to
 // the V layout through a 16 x G slot of LDS private to the wave.  Keys
 // (index-list entries) are fetched one block ahead of the K/V rows, and the
 // K/V rows one block ahead of their use.
-template <int NW, int DH, int G, class Rows, bool RING_WRITE>
+template <int NW, typename T, int DH, int G, class Rows, bool RING_WRITE>
 __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh, int r0, int r1, Rows rows,
                                            const char *kbase, const char *vbase, char *ringK, char *ringV,
-                                           QOperand<DH> &qo, RingCount &cnt, float *s_p,
+                                           QOperand<T, DH, G> &qo, RingCount &cnt, float *s_p,
                                            WaveState<G, DH / 16> &st) {
-    constexpr int SL = DH / 32, VD = DH / 16, RB = DH * 2;
-    constexpr int VB = VD * 2;                 // bytes of V per lane per quarter: 8, 16 or 32
+    using off_t = row_off_t<T>;
+    constexpr int RB = DH * (int)sizeof(T);    // bytes of a row
+    constexpr int SL = RB / 64, VD = DH / 16;  // 16-byte words of K per lane; output dims per lane
+    constexpr int VE = Vec16<T>::N;            // elements per 16-byte word
+    constexpr int VB = VD * (int)sizeof(T);    // bytes of V per lane per quarter: 8 to 64
+    constexpr int NH = kLaneHeads<G>;
     constexpr int VW = VB >= 16 ? VB / 16 : 1; // 16-byte words (or one 8-byte word)
     constexpr int BSTRIDE = NW * 16;
-    constexpr bool kDoubleBuffer = DH <= CMC_DOUBLE_BUFFER_MAX_DH;
+    // The next block's rows in a second register set while this block is
+    // computed, where both fit 256 registers (two waves per SIMD); else the
+    // other waves' loads cover a block's compute.
+    constexpr bool kDoubleBuffer = RB <= CMC_DOUBLE_BUFFER_MAX_ROW && !(sizeof(T) == 2 && G > 4 && RB > 128);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r16 = lane & 15, q4 = lane >> 4, kq = lane & 3, dg = lane >> 2;
-    const uint32_t koff = 16u * q4;        // + 64 * i for slice i
-    const uint32_t voff = (uint32_t)VB * dg;
+    const uint32_t koff = 16u * q4;  // + 64 * i for chunk i
+    const uint32_t voff = (uint32_t)(VB < 16 ? VB : 16) * dg;  // + 256 * j for word j
+    const bool upper = (q4 & 1) != 0;  // G = 8: this lane's heads are 4 .. 7
 
     int blk = r0 + wave * 16;
     if (blk >= r1) return;  // wave-uniform
@@ -409,13 +469,13 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
 #define CMC_LOAD(B0_, K_, V_, KR_, VR_)                                                                \
     do {                                                                                             \
         {                                                                                            \
-            const uint32_t o = (uint32_t)rows.slot(min((B0_) + r16, r1 - 1), K_) * RB + koff;       \
+            const off_t o = (off_t)rows.slot(min((B0_) + r16, r1 - 1), K_) * RB + koff;             \
             _Pragma("unroll") for (int i = 0; i < SL; ++i) KR_[i] = ld16(kbase + o + 64 * i);        \
         }                                                                                            \
         _Pragma("unroll") for (int qq = 0; qq < 4; ++qq) {                                           \
-            const uint32_t o = (uint32_t)rows.slot(min((B0_) + 4 * qq + kq, r1 - 1), V_[qq]) * RB + voff; \
+            const off_t o = (off_t)rows.slot(min((B0_) + 4 * qq + kq, r1 - 1), V_[qq]) * RB + voff;  \
             if constexpr (VB >= 16) {                                                                \
-                _Pragma("unroll") for (int j = 0; j < VW; ++j) VR_[qq][j] = ld16<true>(vbase + o + 16 * j);  \
+                _Pragma("unroll") for (int j = 0; j < VW; ++j) VR_[qq][j] = ld16<true>(vbase + o + 256 * j);  \
             } else {                                                                                 \
                 const uint2 t = *reinterpret_cast<const uint2 *>(vbase + o);                         \
                 VR_[qq][0] = make_uint4(t.x, t.y, 0, 0);                                             \
@@ -431,32 +491,36 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
         /* phase end may have been loaded before r1 was limited by the count */                     \
         const bool bfull = (B0_) + 16 <= r1 && rows.all_valid((B0_), (B0_) + 16);                   \
         const bool kval = (B0_) + r16 < r1 && (bfull || rows.valid((B0_) + r16));                    \
-        floatx4 c = {0.f, 0.f, 0.f, 0.f};                                                            \
-        _Pragma("unroll") for (int i = 0; i < SL; ++i) {                                             \
-            const bf16x8 kbf = __builtin_bit_cast(bf16x8, KR_[i]);                                   \
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qo.hi[i], kbf, c, 0, 0, 0);                 \
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qo.lo[i], kbf, c, 0, 0, 0);                 \
+        const floatx4 c = qo.scores(KR_);                                                            \
+        float pk[NH], mbs[G];                                                                        \
+        /* the lane's heads' maxima first, in straight-line code, so their chains interleave; */     \
+        /* with eight heads the other four come from the neighbouring lane row */                    \
+        _Pragma("unroll") for (int g = 0; g < NH; ++g) {                                             \
+            const float mx = lane_max16(kval ? c[g] : -INFINITY);                                    \
+            if constexpr (G > 4) pair_rows16(mx, mbs[g], mbs[(g + 4) % G]);                          \
+            else mbs[g] = mx;                                                                        \
         }                                                                                            \
-        float pk[G], mbs[G];                                                                         \
-        /* the G heads' maxima first, in straight-line code, so their chains interleave */            \
-        _Pragma("unroll") for (int g = 0; g < G; ++g) mbs[g] = lane_max16(kval ? c[g] : -INFINITY);      \
         _Pragma("unroll") for (int g = 0; g < G; ++g) {                                              \
-            const float sc = kval ? c[g] : -INFINITY;                                                \
             const float mb = mbs[g];                                                                 \
             if (mb > st.m[g]) {                                                                      \
                 if (st.m[g] != -INFINITY) { /* before the first valid key l and acc are 0 */         \
                     const float alpha = fast_exp2(st.m[g] - mb);                                     \
-                    st.l[g] *= alpha;                                                                \
+                    if constexpr (G > 4) st.l[g % NH] *= (g >= 4) == upper ? alpha : 1.f;            \
+                    else st.l[g] *= alpha;                                                           \
                     _Pragma("unroll") for (int i = 0; i < VD; ++i) st.acc[g][i] *= alpha;            \
                 }                                                                                    \
                 st.m[g] = mb;                                                                        \
             }                                                                                        \
+        }                                                                                            \
+        _Pragma("unroll") for (int g = 0; g < NH; ++g) {                                             \
+            const float ma = st.m[g], mb = st.m[(g + 4) % G];                                        \
+            const float m = G > 4 && upper ? mb : ma;                                                \
             /* a masked key weighs 0 (also before any valid key: m is -inf) */                       \
-            pk[g] = kval ? fast_exp2(sc - st.m[g]) : 0.f;                                            \
+            pk[g] = kval ? fast_exp2(c[g] - m) : 0.f;                                                \
             st.l[g] += pk[g];                                                                        \
         }                                                                                            \
-        if (q4 == 0) {                                                                               \
-            _Pragma("unroll") for (int g = 0; g < G; ++g) s_p[r16 * G + g] = pk[g];                 \
+        if (q4 < G / NH) {                                                                           \
+            _Pragma("unroll") for (int g = 0; g < NH; ++g) s_p[r16 * G + q4 * NH + g] = pk[g];      \
         }                                                                                            \
         wave_lds_sync();                                                                             \
         _Pragma("unroll") for (int qq = 0; qq < 4; ++qq) {                                           \
@@ -471,25 +535,25 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
             float pv[G];                                                                             \
             _Pragma("unroll") for (int g = 0; g < G; ++g) pv[g] = s_p[(4 * qq + kq) * G + g];         \
             _Pragma("unroll") for (int j = 0; j < VW; ++j) {                                         \
-                float vf[8];                                                                         \
-                Vec16<uint16_t>::widen(VR_[qq][j], vf);                                              \
+                float vf[VE];                                                                        \
+                Vec16<T>::widen(VR_[qq][j], vf);                                                     \
                 _Pragma("unroll") for (int g = 0; g < G; ++g)                                        \
-                    _Pragma("unroll") for (int e = 0; e < (VD < 8 ? VD : 8); ++e)                    \
-                        st.acc[g][8 * j + e] = fmaf(pv[g], vf[e], st.acc[g][8 * j + e]);             \
+                    _Pragma("unroll") for (int e = 0; e < (VD < VE ? VD : VE); ++e)                  \
+                        st.acc[g][VE * j + e] = fmaf(pv[g], vf[e], st.acc[g][VE * j + e]);           \
             }                                                                                        \
         }                                                                                            \
         wave_lds_sync();                                                                             \
         if constexpr (RING_WRITE) {                                                                  \
             if ((B0_) + r16 < r1) {                                                                  \
-                const uint32_t o = (uint32_t)rows.ring_slot((B0_) + r16) * RB + koff;                \
+                const off_t o = (off_t)rows.ring_slot((B0_) + r16) * RB + koff;                      \
                 _Pragma("unroll") for (int i = 0; i < SL; ++i) st16(ringK + o + 64 * i, KR_[i]);     \
             }                                                                                        \
             _Pragma("unroll") for (int qq = 0; qq < 4; ++qq) {                                       \
                 const int vrow = (B0_) + 4 * qq + kq;                                                \
                 if (vrow < r1) {                                                                     \
-                    const uint32_t o = (uint32_t)rows.ring_slot(vrow) * RB + voff;                   \
+                    const off_t o = (off_t)rows.ring_slot(vrow) * RB + voff;                         \
                     if constexpr (VB >= 16) {                                                        \
-                        _Pragma("unroll") for (int j = 0; j < VW; ++j) st16(ringV + o + 16 * j, VR_[qq][j]); \
+                        _Pragma("unroll") for (int j = 0; j < VW; ++j) st16(ringV + o + 256 * j, VR_[qq][j]);\
                     } else {                                                                         \
                         *reinterpret_cast<uint2 *>(ringV + o) = make_uint2(VR_[qq][0].x, VR_[qq][0].y); \
                     }                                                                                \
@@ -506,7 +570,7 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
     do {                                          \
         if (!qo.ready) {                          \
             cnt.load(p.win_count, b);             \
-            load_q_operand<DH, G>(p, b, kvh, qo.hi, qo.lo); \
+            qo.load(p, b, kvh);                   \
             qo.ready = true;                      \
         }                                         \
         rows.resolve(cnt);                        \
@@ -522,8 +586,6 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
     // past the end would be drained by the barrier after the loop).
     int kc, kvc[4], kn, kvn[4];
     if constexpr (!kDoubleBuffer) {
-        // Wide heads: one register set (two would cost an extra wave per SIMD
-        // of occupancy); the index entries are still fetched a block ahead.
         uint4 kr[SL], vr[4][VW];
         CMC_KEYS(blk, kc, kvc);
 #pragma unroll 1
@@ -575,11 +637,13 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
 #undef CMC_AFTER_FIRST_LOAD
 }
 
-template <int NW, int DH, int G, bool IX>
+template <int NW, typename T, int DH, int G, bool IX>
 __device__ __forceinline__ void mfma_loop(const DecodeParams &p, int b, int kvh, int kb, int c0, int c1,
-                                          RingCount &cnt, float *s_p, WaveState<G, DH / 16> &st) {
-    QOperand<DH> qo;
+                                          RingCount &cnt, float *s_p, uint4 *s_q, WaveState<G, DH / 16> &st) {
+    QOperand<T, DH, G> qo;
+    qo.lds = s_q;
     qo.ready = false;
+    constexpr size_t RB = DH * sizeof(T);
     const size_t head = (size_t)b * p.Hkv + kvh;
     const int T_new = p.W > 0 ? p.T_new : 0;
     const int pool_end = kb, ring_end = kb + p.W;
@@ -587,126 +651,34 @@ __device__ __forceinline__ void mfma_loop(const DecodeParams &p, int b, int kvh,
     // pool rows
     {
         const PoolRows<IX> rows{p.idx, (size_t)b * p.k, p.N > 0 ? p.N - 1 : 0};
-        const char *kb = static_cast<const char *>(p.cme_k) + head * (size_t)p.N * DH * 2;
-        const char *vb = static_cast<const char *>(p.cme_v) + head * (size_t)p.N * DH * 2;
-        mfma_phase<NW, DH, G, PoolRows<IX>, false>(p, b, kvh, c0, min(c1, pool_end), rows, kb, vb, nullptr, nullptr, qo,
-                                               cnt, s_p, st);
+        const char *kb = static_cast<const char *>(p.cme_k) + head * (size_t)p.N * RB;
+        const char *vb = static_cast<const char *>(p.cme_v) + head * (size_t)p.N * RB;
+        mfma_phase<NW, T, DH, G, PoolRows<IX>, false>(p, b, kvh, c0, min(c1, pool_end), rows, kb, vb, nullptr, nullptr,
+                                                  qo, cnt, s_p, st);
     }
     if (p.W > 0) {
-        char *wk = static_cast<char *>(p.win_k) + head * (size_t)p.W * DH * 2;
-        char *wv = static_cast<char *>(p.win_v) + head * (size_t)p.W * DH * 2;
+        char *wk = static_cast<char *>(p.win_k) + head * (size_t)p.W * RB;
+        char *wv = static_cast<char *>(p.win_v) + head * (size_t)p.W * RB;
         // the W ring slots in physical order, masked by the count
         const RingRows rr{pool_end, T_new, p.W};
-        mfma_phase<NW, DH, G, RingRows, false>(p, b, kvh, max(c0, pool_end), min(c1, ring_end), rr, wk, wv, nullptr,
-                                               nullptr, qo, cnt, s_p, st);
+        mfma_phase<NW, T, DH, G, RingRows, false>(p, b, kvh, max(c0, pool_end), min(c1, ring_end), rr, wk, wv, nullptr,
+                                                  nullptr, qo, cnt, s_p, st);
         // rows appended in this call
         if (T_new > 0) {
             const NewRows nr{ring_end, p.W};
-            const char *nk = static_cast<const char *>(p.new_k) + head * (size_t)T_new * DH * 2;
-            const char *nv = static_cast<const char *>(p.new_v) + head * (size_t)T_new * DH * 2;
-            mfma_phase<NW, DH, G, NewRows, true>(p, b, kvh, max(c0, ring_end), c1, nr, nk, nv, wk, wv, qo, cnt, s_p,
-                                                 st);
+            const char *nk = static_cast<const char *>(p.new_k) + head * (size_t)T_new * RB;
+            const char *nv = static_cast<const char *>(p.new_v) + head * (size_t)T_new * RB;
+            mfma_phase<NW, T, DH, G, NewRows, true>(p, b, kvh, max(c0, ring_end), c1, nr, nk, nv, wk, wv, qo, cnt, s_p,
+                                                    st);
         }
     }
     // Wave totals: l over the 16 keys of one lane row (rows hold copies),
     // acc over the 4 keys sharing a dim group.
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        st.l[g] = lane_reduce<OpSum, 1, 16>(st.l[g]);
+        if (g < kLaneHeads<G>) st.l[g] = lane_reduce<OpSum, 1, 16>(st.l[g]);
 #pragma unroll
         for (int i = 0; i < DH / 16; ++i) st.acc[g][i] = lane_reduce<OpSum, 1, 4>(st.acc[g][i]);
-    }
-}
-
-// --------------------------------------------------------------- VALU loop
-
-template <int NW, typename T, int DH, int G, int U>
-__device__ __forceinline__ void valu_loop(const DecodeParams &p, const RowMap<T> &rm, int b, int kvh, int c0,
-                                          int c1, WaveState<G, Vec16<T>::N> &st) {
-    constexpr int VEC = Vec16<T>::N;
-    constexpr int LPR = DH / VEC;
-    constexpr int RPW = kWave / LPR;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int grp = lane / LPR, e = lane % LPR;
-    CMC_UNPACK_ROWMAP(rm);
-
-    float qf[G][VEC];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const float4 *qp = reinterpret_cast<const float4 *>(
-            p.q + ((size_t)b * p.Hq + (size_t)kvh * G + g) * DH + e * VEC);
-#pragma unroll
-        for (int i = 0; i < VEC / 4; ++i) {
-            const float4 t = qp[i];
-            qf[g][4 * i + 0] = t.x * p.qscale;
-            qf[g][4 * i + 1] = t.y * p.qscale;
-            qf[g][4 * i + 2] = t.z * p.qscale;
-            qf[g][4 * i + 3] = t.w * p.qscale;
-        }
-    }
-
-    constexpr int STRIDE = NW * RPW;
-    for (int r0 = c0 + wave * RPW; r0 < c1; r0 += STRIDE * U) {
-        uint4 kr[U], vr[U];
-        bool ok[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int row = r0 + u * STRIDE + grp;
-            ok[u] = row < c1 && VALID(row);
-            kr[u] = vr[u] = make_uint4(0, 0, 0, 0);
-            if (ok[u]) {
-                const RowPtrs<T> rp = LOCATE(row);
-                kr[u] = ld16(rp.k + e * VEC);
-                vr[u] = ld16(rp.v + e * VEC);
-                if (rp.rk) {
-                    st16(rp.rk + e * VEC, kr[u]);
-                    st16(rp.rv + e * VEC, vr[u]);
-                }
-            }
-        }
-        float sc[U][G];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float kf[VEC];
-            Vec16<T>::widen(kr[u], kf);
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                float d = 0.f;
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) d = fmaf(qf[g][i], kf[i], d);
-                d = lane_reduce<OpSum, 1, LPR>(d);
-                sc[u][g] = ok[u] ? d : -INFINITY;
-            }
-        }
-        float vf[U][VEC];
-#pragma unroll
-        for (int u = 0; u < U; ++u) Vec16<T>::widen(vr[u], vf[u]);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float mb = sc[0][g];
-#pragma unroll
-            for (int u = 1; u < U; ++u) mb = fmaxf(mb, sc[u][g]);
-            mb = lane_reduce<OpMax, LPR, kWave>(mb);
-            const float mn = fmaxf(st.m[g], mb);
-            const float alpha = mn == -INFINITY ? 1.f : exp2f(st.m[g] - mn);  // nothing valid yet: keep
-            st.l[g] *= alpha;
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) st.acc[g][i] *= alpha;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float pu = ok[u] ? exp2f(sc[u][g] - mn) : 0.f;
-                st.l[g] += pu;
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) st.acc[g][i] = fmaf(pu, vf[u][i], st.acc[g][i]);
-            }
-            st.m[g] = mn;
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        st.l[g] = lane_reduce<OpSum, LPR, kWave>(st.l[g]);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) st.acc[g][i] = lane_reduce<OpSum, LPR, kWave>(st.acc[g][i]);
     }
 }
 
@@ -760,13 +732,19 @@ __device__ __forceinline__ float combine_waves(const float (&sm)[NW][G], const f
     return M;
 }
 
+// Waves per SIMD the compiler must leave registers for, where its own choice
+// would be one: eight heads (but not of 256, whose accumulators alone take
+// half of the registers) and 256-wide fp32 rows.
+template <typename T, int DH, int G>
+constexpr int kMinWaves = G * DH <= 1024 && (G > 4 || sizeof(T) * DH > 512) ? 2 : 1;
+
 // The leading arguments are the fields the first K/V loads need (info packs
 // S, new_split, whether k_len is given, and T_new); they arrive in
 // SGPRs at wave launch (kernel-argument preloading, 14 dwords), so those
 // loads never wait for the kernel-argument segment.  The rest of the
 // parameters come from `pm`.
-template <int NW, typename T, int DH, int G, bool MF, bool IX>
-__global__ __launch_bounds__(NW * kWave) void decode_kernel(const void *cme_k, const void *cme_v, void *win_k,
+template <int NW, typename T, int DH, int G, bool IX>
+__global__ __launch_bounds__(NW * kWave, (kMinWaves<T, DH, G>)) void decode_kernel(const void *cme_k, const void *cme_v, void *win_k,
                                                             void *win_v, int k, int W, int N, int Hkv, int chunk,
                                                             int info, DecodeParams pm) {
     DecodeParams p = pm;
@@ -784,23 +762,13 @@ __global__ __launch_bounds__(NW * kWave) void decode_kernel(const void *cme_k, c
     const bool has_klen = (info >> 10) & 1;
     p.T_new = (int)((unsigned)info >> 16);
     constexpr int kThreads = NW * kWave;
-    constexpr int VEC = MF ? DH / 16 : Vec16<T>::N;  // output dims a lane accumulates
+    constexpr int VEC = DH / 16;  // output dims a lane accumulates
+    constexpr int NH = kLaneHeads<G>;
     const int s = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
-    // Ring count.  MFMA path: fetched by each wave after its first K/V loads
-    // (RingCount), so they never wait for it.  VALU path: read up front (its
-    // row map resolves ring slots before the loads).
+    // Fetched by each wave after its first K/V loads, so they never wait for it.
     RingCount cnt{0, false};
-    int cnt0 = 0, slot0 = 0;
-    if (p.W > 0) {
-        if constexpr (!MF) {
-            cnt.raw = p.win_count[b];
-            cnt.loaded = true;
-            cnt0 = cnt.raw < 0 ? 0 : cnt.raw;
-            slot0 = cnt0 % p.W;
-        }
-    }
     int kb = p.k;  // pool rows of this sequence
     if (has_klen) {
         const int v = p.k_len[b];
@@ -821,7 +789,6 @@ __global__ __launch_bounds__(NW * kWave) void decode_kernel(const void *cme_k, c
         c0 = s * p.chunk;
         c1 = s == p.S - 1 ? L : min(c0 + p.chunk, L);
     }
-    const RowMap<T> rm = make_rowmap<T>(p, b, kvh, DH, kb, slot0, min(cnt0, p.W));
 
     // Ring count.  It may be advanced only after every wave of the
     // sequence's workgroups has read it.  Each wave stores the count it read
@@ -841,15 +808,11 @@ __global__ __launch_bounds__(NW * kWave) void decode_kernel(const void *cme_k, c
 
     WaveState<G, VEC> st;
     st.init();
-    if constexpr (MF) {
-        __shared__ float s_pw[NW][16 * G];
-        mfma_loop<NW, DH, G, IX>(p, b, kvh, kb, c0, c1, cnt, s_pw[threadIdx.x >> 6], st);
-    } else {
-        constexpr int U = (sizeof(T) == 2 && DH >= 128) ? 4 : 2;
-        valu_loop<NW, T, DH, G, U>(p, rm, b, kvh, c0, c1, st);
-    }
+    __shared__ __attribute__((aligned(16))) float s_pw[NW][16 * G];
+    __shared__ uint4 s_q[NW][QOperand<T, DH, G>::kLdsWords];
+    mfma_loop<NW, T, DH, G, IX>(p, b, kvh, kb, c0, c1, cnt, s_pw[threadIdx.x >> 6], s_q[threadIdx.x >> 6], st);
     if (p.W > 0) cnt.load(p.win_count, b);  // a wave without K/V rows
-    const int cnt_now = MF ? cnt.value() : cnt0;
+    const int cnt_now = cnt.value();
 #define CMC_BUMP()                                                                         \
     do {                                                                                 \
         if (bump && prev == (unsigned)(p.Hkv - 1)) { /* one lane per sequence */       \
@@ -858,10 +821,10 @@ __global__ __launch_bounds__(NW * kWave) void decode_kernel(const void *cme_k, c
         }                                                                                \
     } while (0)
 
-    // Lanes holding each dim group after the wave reduction.
-    constexpr int LPR = MF ? 4 : DH / Vec16<T>::N;         // lanes per dim group stride
-    const bool holder = MF ? ((lane & 3) == 0) : (lane < LPR);
-    const int dbase = MF ? (lane >> 2) * VEC : lane * VEC;
+    // One lane of each dim group holds it after the wave reduction.
+    const bool holder = (lane & 3) == 0;
+    constexpr int VL = VEC < Vec16<T>::N ? VEC : Vec16<T>::N;  // consecutive dims a lane holds: of word j, dims
+                                                                // 16 VL j + VL (lane / 4) .. + VL - 1
 
     __shared__ float s_acc[NW][G][DH];
     __shared__ float s_m[NW][G], s_l[NW][G];
@@ -869,13 +832,14 @@ __global__ __launch_bounds__(NW * kWave) void decode_kernel(const void *cme_k, c
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) s_acc[wave][g][dbase + i] = st.acc[g][i];
+            for (int i = 0; i < VEC; ++i) s_acc[wave][g][(i / VL) * 16 * VL + (lane >> 2) * VL + i % VL] = st.acc[g][i];
     }
-    if (lane == 0) {
+    if ((lane & 15) == 0 && lane / 16 < G / NH) {  // lanes 0 (and, G = 8, 16): the heads they hold
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            s_m[wave][g] = st.m[g];
-            s_l[wave][g] = st.l[g];
+        for (int g = 0; g < NH; ++g) {
+            const float ma = st.m[g], mb = st.m[(g + 4) % G];
+            s_m[wave][(lane / 16) * NH + g] = G > 4 && lane != 0 ? mb : ma;
+            s_l[wave][(lane / 16) * NH + g] = st.l[g];
         }
     }
     __shared__ int s_cnt[NW];
@@ -1024,19 +988,18 @@ __global__ __launch_bounds__(NW * kWave) void decode_kernel(const void *cme_k, c
 template <typename T, int DH, int G>
 hipError_t launch3(const DecodeParams &p, hipStream_t stream) {
     dim3 grid(p.S, p.Hkv, p.B);
-    constexpr bool kMf = sizeof(T) == 2 && G >= CMC_MFMA_MIN_G && G <= 4;
     if (p.S < 1 || p.S > 0xFF || p.T_new < 0 || p.T_new > kMaxAppendRows) return hipErrorInvalidValue;
     const int info = p.S | (p.new_split << 8) | ((p.k_len != nullptr) << 10) | (p.T_new << 16);
-    const bool ix = kMf && p.idx != nullptr;
+    const bool ix = p.idx != nullptr;
 #define CMC_LAUNCH(NW_, IX_)                                                                                     \
-    decode_kernel<NW_, T, DH, G, kMf, IX_><<<grid, NW_ * kWave, 0, stream>>>(p.cme_k, p.cme_v, p.win_k, p.win_v, \
+    decode_kernel<NW_, T, DH, G, IX_><<<grid, NW_ * kWave, 0, stream>>>(p.cme_k, p.cme_v, p.win_k, p.win_v, \
                                                                              p.k, p.W, p.N, p.Hkv, p.chunk, info, p)
     if (p.waves == 4) {
-        if (ix) CMC_LAUNCH(4, kMf);
+        if (ix) CMC_LAUNCH(4, true);
         else CMC_LAUNCH(4, false);
     } else if constexpr (decode_waves_ok(8, G, DH)) {
         if (p.waves != 8) return hipErrorInvalidValue;
-        if (ix) CMC_LAUNCH(8, kMf);
+        if (ix) CMC_LAUNCH(8, true);
         else CMC_LAUNCH(8, false);
     } else {
         return hipErrorInvalidValue;

@@ -119,6 +119,14 @@ __device__ __forceinline__ float combine_xor32(float v) {
     return Op::f(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// v of the even and of the odd 16-lane row of this lane's pair of rows.
+__device__ __forceinline__ void pair_rows16(float v, float &even, float &odd) {
+    const unsigned u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    even = __uint_as_float(r[0]);
+    odd = __uint_as_float(r[1]);
+}
+
 // Combine v over the lane-index bits selected by [LO, HI) (powers of two):
 // lane_reduce<Op, 1, 16> reduces within aligned 16-lane groups,
 // lane_reduce<Op, 16, 64> across the four 16-lane rows, etc.

@@ -9,10 +9,10 @@ namespace cmc {
 
 // A decode workgroup has 4 or 8 waves, each streaming its own 16-key blocks;
 // the workgroup combines them in LDS.  8 waves (at most 256 VGPRs each) are
-// built only for heads whose kernels fit that without spilling: Dh <= 128
-// with G <= 4, or one query head per kv head.
+// built only for heads whose kernels fit that without spilling: Dh <= 128, or
+// one query head per kv head.
 constexpr bool decode_waves_ok(int waves, int G, int Dh) {
-    return waves == 4 || (waves == 8 && ((Dh <= 128 && G <= 4) || G == 1));
+    return waves == 4 || (waves == 8 && (Dh <= 128 || G == 1));
 }
 
 struct DecodeParams {
@@ -41,15 +41,16 @@ struct DecodeParams {
 // Rows one decode call may append (the launch packs T_new into 16 bits).
 constexpr int kMaxAppendRows = 65535;
 
-// Key-axis split plan; depends only on sizes, so the workspace query and the
-// launch agree.  Workspace layout: [sequence counters | pair counters]
-// (zero between calls), then the per-split partials.
+// Key-axis split plan; depends only on sizes and on whether the call appends
+// rows, so the workspace query (the larger of the two plans) and the launch
+// agree.  Workspace layout: [sequence counters | pair counters] (zero between
+// calls), then the per-split partials.
 struct DecodePlan {
     int S = 0, chunk = 0, waves = 4;  // S splits over the k + W rows
-    int S_alloc = 0;                  // partials reserved: S, plus one for appended rows when S > 1 and W > 0
+    bool own_append = false;          // one more split takes the appended rows
     size_t counter_bytes = 0, ml_bytes = 0, acc_bytes = 0, total = 0;
 };
-DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W);
+DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W, bool append);
 
 hipError_t launch_two_tier_decode(const DecodeParams &p, bool bf16, int G, int Dh, hipStream_t stream);
 float decode_qscale(float scale);

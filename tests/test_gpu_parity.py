@@ -346,7 +346,7 @@ def test_decode_step_fused(orc, dtype, Dh, G, t_new, W, fill):
     (48, 4, 4, 128, "bf16", 64, 37, 75, 75),      # 192 pairs: one 8-wave workgroup each
     (32, 8, 4, 128, "bf16", 400, 300, 500, 500),  # 256 pairs, several blocks per wave, ragged tail
     (32, 8, 4, 128, "bf16", 20, 0, 16, 3),        # 256 pairs, fewer keys than waves
-    (64, 4, 8, 64, "bf16", 40, 20, 33, 10),       # VALU path (G = 8), ring not yet full
+    (64, 4, 8, 64, "bf16", 40, 20, 33, 10),       # G = 8, ring not yet full
     (32, 8, 1, 256, "bf16", 100, 64, 128, 128),   # wide head, G = 1
     (32, 8, 2, 256, "bf16", 40, 30, 50, 50),      # wide head, G = 2: stays on 4 waves
     (40, 5, 2, 128, "f32", 50, 45, 60, 60),       # 200 pairs, fp32
@@ -357,6 +357,18 @@ def test_decode_wide_workgroups(orc, B, Hkv, G, Dh, dtype, N, k, W, fill):
     workgroup per pair; results match the oracle like every other plan."""
     _decode_case(orc, B=B, Hq=G * Hkv, Hkv=Hkv, Dh=Dh, N=N, k=k, W=W, fill=fill, dtype=dtype,
                  seed=B * Hkv + G + Dh, steps=3, fused=W > 0)
+
+
+@pytest.mark.parametrize("Dh,G,dtype", [(128, 4, "bf16"), (64, 1, "f32"), (128, 8, "bf16"), (256, 8, "f32")])
+@pytest.mark.parametrize("pairs", [128, 129, 167, 168, 256, 257, 367, 368, 513])
+def test_decode_plan_edges(orc, Dh, G, dtype, pairs):
+    """(sequence, kv head) pair counts on both sides of every line of the
+    split plan, with and without the fused append (whose rows take a split of
+    their own), from one zeroed workspace of the queried size; key counts that
+    are not whole blocks."""
+    for fused in (False, True):
+        _decode_case(orc, B=pairs, Hq=G, Hkv=1, Dh=Dh, N=90, k=77, W=70, fill=69, dtype=dtype, seed=pairs + G + Dh,
+                     steps=2, fused=fused)
 
 
 def _random_decode_config(seed):
@@ -397,8 +409,8 @@ def test_decode_random_configs(orc, seed):
     (2, 2, 1, 64, "bf16", 90, 40, 700, 333),      # G = 1, many splits
     (32, 8, 4, 128, "bf16", 64, 32, 300, 45),     # 256 pairs: one 8-wave workgroup each (S = 1)
     (3, 2, 2, 256, "bf16", 50, 20, 200, 17),      # wide head, single-buffered loop
-    (2, 2, 8, 128, "bf16", 50, 20, 200, 17),      # G = 8: VALU path
-    (2, 2, 4, 128, "f32", 50, 20, 200, 17),       # fp32: VALU path
+    (2, 2, 8, 128, "bf16", 50, 20, 200, 17),      # G = 8
+    (2, 2, 4, 128, "f32", 50, 20, 200, 17),       # fp32
 ])
 def test_decode_unfilled_slots_hold_nan(orc, fused, B, Hkv, G, Dh, dtype, N, k, W, fill):
     """Ring slots that were never filled may hold anything, NaN included:
