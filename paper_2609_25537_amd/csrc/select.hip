@@ -10,8 +10,9 @@
 //
 // topk_kernel: one 1024-thread workgroup per sequence.  Scores become
 // order-preserving uint32 keys (kept in registers, ceil(N / 1024) per thread
-// rounded up to a power of two, at most 32, so N <= 32768).  The k-th largest key T is found bit by bit from the top: T is the
-// largest value with count(key >= T) >= k, one block-wide count per bit.
+// rounded up to a power of two, at most 32, so N <= 32768).  The k-th largest
+// key T is found from the top, one bit per round, or three with few keys per
+// thread: T is the largest value with count(key >= T) >= k.
 // Then every key > T is taken, plus the first (k - count(key > T)) keys equal
 // to T in index order (ties go to the earlier document position).  Two
 // block-wide exclusive scans over the threads' contiguous index ranges give
@@ -50,39 +51,61 @@ __device__ __forceinline__ void score_rows(const SelectParams &p, int b, int j0,
     }
     constexpr int E = 16 / EB;  // elements per 16-byte vector
     const int DV = p.D / E;
-#pragma unroll 2
-    for (int c = lane; c < DV; c += kWave) {
-        float qv[E];
+    // One row per wave: four key vectors per lane in flight at once, past the
+    // row's end clamped into it and taken as zeros (the sums keep their
+    // order).  Few waves run then, so each has to keep more in flight: 2048
+    // rows of 4096 fp32 keys, their top-k and gather 22.0 us with two in
+    // flight, 21.2 with four; 100 rows of 1024 for 20 sequences 15.8 / 15.4.
+    // Four rows per wave keep eight in flight.
+    constexpr int U = R == 1 ? 4 : 1;
+#pragma unroll(R == 1 ? 1 : 2)
+    for (int c0 = lane; c0 < DV; c0 += U * kWave) {
+        f32x4 ahead[U];
+        if constexpr (U > 1) {
 #pragma unroll
-        for (int i = 0; i < E / 4; ++i) {
-            const float4 t = q4[c * (E / 4) + i];
-            qv[4 * i + 0] = t.x;
-            qv[4 * i + 1] = t.y;
-            qv[4 * i + 2] = t.z;
-            qv[4 * i + 3] = t.w;
+            for (int u = 0; u < U; ++u)
+                ahead[u] = __builtin_nontemporal_load(
+                    reinterpret_cast<const f32x4 *>(rows[0] + (size_t)min(c0 + u * kWave, DV - 1) * 16));
         }
 #pragma unroll
-        for (int e = 0; e < E; ++e) qq = fmaf(qv[e], qv[e], qq);
+        for (int u = 0; u < U; ++u) {
+            const int c = U > 1 ? min(c0 + u * kWave, DV - 1) : c0;
+            const bool in = U == 1 || c0 + u * kWave < DV;
+            float qv[E];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            // Non-temporal: each key row is read once (0.81 -> 0.74 ms on the
-            // 64 x 4096 x 4096 fp32 Mistral-shaped batch).
-            const f32x4 mw = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rows[r] + (size_t)c * 16));
-            float mv[E];
-            if constexpr (BF16) {
-                const uint4 u = make_uint4(__float_as_uint(mw.x), __float_as_uint(mw.y), __float_as_uint(mw.z),
-                                           __float_as_uint(mw.w));
-                Vec16<uint16_t>::widen(u, mv);
-            } else {
-                mv[0] = mw.x;
-                mv[1] = mw.y;
-                mv[2] = mw.z;
-                mv[3] = mw.w;
+            for (int i = 0; i < E / 4; ++i) {
+                const float4 t = q4[c * (E / 4) + i];
+                qv[4 * i + 0] = in ? t.x : 0.f;
+                qv[4 * i + 1] = in ? t.y : 0.f;
+                qv[4 * i + 2] = in ? t.z : 0.f;
+                qv[4 * i + 3] = in ? t.w : 0.f;
             }
 #pragma unroll
-            for (int e = 0; e < E; ++e) dot[r] = fmaf(mv[e], qv[e], dot[r]);
+            for (int e = 0; e < E; ++e) qq = fmaf(qv[e], qv[e], qq);
 #pragma unroll
-            for (int e = 0; e < E; ++e) nn[r] = fmaf(mv[e], mv[e], nn[r]);
+            for (int r = 0; r < R; ++r) {
+                // Non-temporal: each key row is read once (0.81 -> 0.74 ms on the
+                // 64 x 4096 x 4096 fp32 Mistral-shaped batch).
+                f32x4 mw;
+                if constexpr (U > 1) mw = ahead[u];
+                else mw = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rows[r] + (size_t)c * 16));
+                if (!in) mw = f32x4{0.f, 0.f, 0.f, 0.f};
+                float mv[E];
+                if constexpr (BF16) {
+                    const uint4 w = make_uint4(__float_as_uint(mw.x), __float_as_uint(mw.y), __float_as_uint(mw.z),
+                                               __float_as_uint(mw.w));
+                    Vec16<uint16_t>::widen(w, mv);
+                } else {
+                    mv[0] = mw.x;
+                    mv[1] = mw.y;
+                    mv[2] = mw.z;
+                    mv[3] = mw.w;
+                }
+#pragma unroll
+                for (int e = 0; e < E; ++e) dot[r] = fmaf(mv[e], qv[e], dot[r]);
+#pragma unroll
+                for (int e = 0; e < E; ++e) nn[r] = fmaf(mv[e], mv[e], nn[r]);
+            }
         }
     }
 }
@@ -181,6 +204,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(SelectParams p) {
     const int cnt = max(0, min(per, nb - j0));
 
     __shared__ float s_part[2][kTopkWaves];
+    __shared__ int s_round[2][PER <= 2 ? kTopkWaves : 1][8];  // two, so that one barrier per round suffices
     __shared__ int s_wave[kTopkWaves];
     int slot = 0;
 
@@ -191,12 +215,48 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(SelectParams p) {
 
     // T = largest value with count(key >= T) >= k.
     uint32_t T = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t cand = T | (1u << bit);
-        int c = 0;
+    if constexpr (PER <= 2) {
+        // Few keys per thread: three bits per round (the first time two), since
+        // a round is bound by its barrier and LDS round trip, not by its
+        // compares.  The counts of all candidates come per wave from ballots
+        // (uniform, no lane reduction); lane 8 g + d then adds candidate d's of
+        // two of the 16 waves and the lanes of one d are summed.  With more
+        // keys per thread the 7 PER ballots cost more than the rounds they
+        // save.  Selection and gather, one bit / three bits per round: 2048
+        // rows of one sequence 24.8 / 22.0 us, 100 rows of 20 sequences 20.6 /
+        // 15.8; 6000 rows of 4 sequences 73.7 / 90.6, 16384 rows 61 / 114.
+        constexpr int BITS = 3;
+        const int lane = tid & 63, wave = tid >> 6;
+        for (int lo = 30; lo >= 0; lo -= BITS) {
+            int mine = 0;
 #pragma unroll
-        for (int i = 0; i < kPerThread; ++i) c += (i < cnt && key[i] >= cand) ? 1 : 0;
-        if (block_count(c, s_part, slot) >= k) T = cand;
+            for (int d = 1; d < 1 << BITS; ++d) {
+                const uint32_t cand = T | ((uint32_t)d << lo);  // one past bit 31 is discarded below
+                int c = 0;
+#pragma unroll
+                for (int i = 0; i < kPerThread; ++i) c += __popcll(__ballot(i < cnt && key[i] >= cand));
+                mine = lane == d ? c : mine;
+            }
+            if (lane < 8) s_round[slot][wave][lane] = mine;
+            __syncthreads();
+            const int d = lane & 7, w = lane >> 3;
+            const float c2 = (float)(s_round[slot][2 * w][d] + s_round[slot][2 * w + 1][d]);  // < 2^24: exact
+            const float total = lane_reduce<OpSum, 8, kWave>(c2);
+            slot ^= 1;
+            // The counts fall with d, so the candidates that qualify are 1 .. some d.
+            const int top = lo + BITS > 32 ? (1 << (32 - lo)) - 1 : (1 << BITS) - 1;
+            const unsigned ok = (unsigned)__ballot(d >= 1 && d <= top && total >= (float)k) & 0xFFu;
+            const uint32_t digit = ok ? 31u - (uint32_t)__builtin_clz(ok) : 0u;
+            T |= digit << lo;
+        }
+    } else {
+        for (int bit = 31; bit >= 0; --bit) {
+            const uint32_t cand = T | (1u << bit);
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < kPerThread; ++i) c += (i < cnt && key[i] >= cand) ? 1 : 0;
+            if (block_count(c, s_part, slot) >= k) T = cand;
+        }
     }
 
     int gt = 0, eq = 0;
