@@ -398,7 +398,10 @@ __global__ __launch_bounds__(256) void bridge_norm_kernel(BridgeParams p) {
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
         const int c = lane + u * kWave;
-        if (c < n4) y4[c] = float4{v[u].x * scale, v[u].y * scale, v[u].z * scale, v[u].w * scale};
+        if (c < n4) {
+            st16_nt(&y4[c], make_uint4(__float_as_uint(v[u].x * scale), __float_as_uint(v[u].y * scale),
+                                       __float_as_uint(v[u].z * scale), __float_as_uint(v[u].w * scale)));
+        }
     }
 }
 
@@ -538,10 +541,19 @@ hipError_t launch_gemm_t(int epi, const GemmParams &g, hipStream_t stream) {
 #endif
 
 hipError_t launch_gemm(int epi, const GemmParams &g, hipStream_t stream) {
+    // The tile by how many of them there are: a grid that leaves CUs idle
+    // costs more than a small tile's extra operand reads.  Whole calls at Hc
+    // = 1280, F = Hd = 4096 in us, 256- / 128- / 64-wide tiles: 48 rows 163 /
+    // 89 / 47, 768 rows 184 / 96 / 85, 1536 rows (96 tiles of 256, 384 of
+    // 128) 192 / 141 / 145, 2304 rows 212 / 190 / 206, 3072 rows (192 tiles
+    // of 256) 215 / 206 / 267, 4096 rows 233 / 279 / 357.
+    const long long t256 = (long long)((g.M + 255) / 256) * (g.N / 256);
+    const long long t128 = (long long)((g.M + 127) / 128) * (g.N / 128);
     if constexpr (CMC_BRIDGE_BIG) {
-        if (g.N % 256 == 0 && g.K % CMC_BRIDGE_BIG_BK == 0)
+        if (g.N % 256 == 0 && g.K % CMC_BRIDGE_BIG_BK == 0 && t256 > 192)
             return launch_gemm_t<128, 64, 2, 4, CMC_BRIDGE_BIG_BK, CMC_BRIDGE_BIG_STAGES>(epi, g, stream);
     }
+    if (t128 < 384) return launch_gemm_t<32, 32, 2, 2, 64, 2>(epi, g, stream);
     constexpr int RS = CMC_BRIDGE_REG_STAGES;
     if (CMC_BRIDGE_BK != 64 && g.K % CMC_BRIDGE_BK == 0)
         return launch_gemm_t<64, 64, 2, 2, CMC_BRIDGE_BK, RS>(epi, g, stream);

@@ -107,6 +107,18 @@ def test_bridge_shapes(orc, M, Hc, F, Hd):
     _run(orc, h, _params(rng, Hc, F, Hd), nu=0.8, what="shapes")
 
 
+@pytest.mark.parametrize("M", [6016, 6017, 6144, 12288, 12289])
+def test_bridge_tile_choice_edges(orc, M):
+    """Row counts on both sides of the lines between the 64-, 128- and
+    256-wide tiles (384 tiles of 128, 192 of 256 for a width of 1024); the rows
+    around every tile edge near the end and random ones checked."""
+    rng = np.random.default_rng(M)
+    h = wl.f32_to_bf16_bits(rng.standard_normal((M, 64)).astype(np.float32))
+    rows = sorted({0, 63, 64, 127, 128, 255, 256, M - 257, M - 256, M - 129, M - 128, M - 65, M - 64, M - 2, M - 1,
+                   *rng.integers(0, M, size=40).tolist()})
+    _run(orc, h, _params(rng, 64, 1024, 256), nu=0.8, rows=rows, what="tile choice")
+
+
 def test_bridge_more_tiles_than_cus(orc):
     """More 256 x 256 tiles than CUs (33 x 8 = 264 for the first layer), so
     workgroups of a persistent grid take several tiles; every row checked."""
