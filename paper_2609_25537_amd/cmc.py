@@ -134,26 +134,51 @@ def _ptr(t) -> Optional[int]:
     if isinstance(t, int):
         return t
     if not t.is_cuda:
-        raise ValueError(f"cmc: tensor of shape {tuple(t.shape)} is on {t.device}; the library takes device tensors")
+        _on_host(t)
     return t.data_ptr()
+
+
+def _on_host(t):
+    raise ValueError(f"cmc: tensor of shape {tuple(t.shape)} is on {t.device}; the library takes device tensors")
+
+
+# torch, and its calls for the current device and that device's current
+# stream as a raw handle, looked up at the first use (importing this module
+# does not import torch).  A decode step's launch takes about 9 us on the GPU
+# and 3 us in the HIP runtime, so what the wrappers do around it counts: the
+# per-call lookups and helper calls are kept out of them (12.0 -> 8.8 us for a
+# batch-1 step).
+_torch = _device_index = _raw_stream = None
+
+
+def _load_torch():
+    global _torch, _device_index, _raw_stream
+    import torch
+    _device_index = torch.cuda.current_device  # also initialises the runtime where that is still to do
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda d: torch.cuda.current_stream(d).cuda_stream)
+    _torch = torch
+    return torch
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _torch is None:
+            _load_torch()
+        return _raw_stream(_device_index())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
 def _kv_dtype(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
+    torch = _torch or _load_torch()
+    d = t.dtype
+    if d is torch.bfloat16:
         return CMC_BF16
-    if t.dtype == torch.float32:
+    if d is torch.float32:
         return CMC_F32
-    raise TypeError(f"expected a float32 or bfloat16 tensor, got {t.dtype}")
+    raise TypeError(f"expected a float32 or bfloat16 tensor, got {d}")
 
 
 def _need(cond: bool, msg: str) -> None:
@@ -171,7 +196,7 @@ def cmc_select_cmes(sel_keys, q_vec, k: int, idx_out=None, scores_out=None, work
                     stream=None):
     """Tier-1 selection.  sel_keys [B][N][D] fp32 or bf16, q_vec [B][D] fp32
     (device).  Returns idx_out [B][k] int32 (ascending)."""
-    import torch
+    torch = _torch or _load_torch()
     _need(sel_keys.dim() == 3 and sel_keys.is_contiguous(), "sel_keys must be contiguous [B][N][D]")
     B, N, D = sel_keys.shape
     _need(q_vec.shape == (B, D) and q_vec.is_contiguous(), "q_vec must be contiguous [B][D]")
@@ -201,7 +226,7 @@ def cmc_select_cmes_ragged(sel_keys, q_vec, n_rows, k: int, q_rows=None, idx_str
     n_rows[b] rows; q_rows[b] pinned question rows (pool rows n_b ..) follow
     the selected ones.  sel_keys fp32 or bf16; n_rows/q_rows [B] int32
     (device).  Returns (idx_out [B][idx_stride] int32, k_out [B] int32)."""
-    import torch
+    torch = _torch or _load_torch()
     _need(sel_keys.dim() == 3 and sel_keys.is_contiguous(), "sel_keys must be contiguous [B][N][D]")
     B, N, D = sel_keys.shape
     _need(q_vec.shape == (B, D) and q_vec.is_contiguous(), "q_vec must be contiguous [B][D]")
@@ -241,7 +266,7 @@ def cmc_locate_window(norms, ctx_len, W: int, mems_per_chunk: int, n_rows=None, 
     """CME-guided Tier-2 window placement.  norms [B][N] fp32, ctx_len [B]
     int32, chunk_offset [B][n_chunks] int32 or None (chunk i at i *
     chunk_tokens).  Returns (alpha [B], start [B]) int32."""
-    import torch
+    torch = _torch or _load_torch()
     _need(norms.dim() == 2 and norms.dtype == torch.float32 and norms.is_contiguous(), "norms [B][N] fp32")
     B, N = norms.shape
     _need(ctx_len.shape == (B,) and ctx_len.dtype == torch.int32 and ctx_len.is_contiguous(), "ctx_len [B] int32")
@@ -277,7 +302,7 @@ def cmc_memory_bridge(h, w1, b1, w2, b2, ln_gamma, ln_beta, nu: float, ln_eps: f
     w2 [Hd][F] bf16, b2/ln_gamma/ln_beta [Hd] fp32 (device).  Returns out
     [M][Hd] fp32; the workspace (if given) then holds the hidden activations
     [M][F] bf16, and h_norms_out (if given, [M] fp32) the norms |h_j|."""
-    import torch
+    torch = _torch or _load_torch()
     bf, f32 = torch.bfloat16, torch.float32
     _need(h.dim() == 2 and h.dtype == bf and h.is_contiguous(), "h must be contiguous bf16 [M][Hc]")
     M, Hc = h.shape
@@ -317,7 +342,7 @@ def cmc_denoise(emb, g: int = 3, tau: float = 0.05, keep_min_every: int = 16, n_
     Returns dict(kept_idx [B][n] int32, kept_count [B] int32, and when asked
     for (a tensor passed, or chunk_tokens > 0) max_cos, keep, chunk_offset,
     n_chunks)."""
-    import torch
+    torch = _torch or _load_torch()
     _need(emb.dim() == 3 and emb.is_contiguous(), "emb must be contiguous [B][n][H]")
     B, n, H = emb.shape
     dev = emb.device
@@ -365,7 +390,7 @@ def cmc_gather_tier1(cme_k, cme_v, idx, k: int, k_len=None, out_k=None, out_v=No
     """Copy the selected rows' K/V into contiguous [B][Hkv][k][Dh] blocks
     (row j = pool row idx[b][j]; idx [B][idx_stride] int32 or None for rows
     0..k-1; k_len [B] int32 or None).  Returns (out_k, out_v)."""
-    import torch
+    torch = _torch or _load_torch()
     _need(cme_k.dim() == 4 and cme_k.is_contiguous() and cme_v.is_contiguous() and cme_v.shape == cme_k.shape,
           "cme_k/v [B][Hkv][N][Dh]")
     B, Hkv, N, Dh = cme_k.shape
@@ -397,7 +422,7 @@ def cmc_window_start(ctx_len: int, W: int, alpha: int) -> int:
 def cmc_window_append(win_k, win_v, win_count, new_k, new_v, stream=None) -> None:
     """Ring append in place.  win_* [B][Hkv][W][Dh], new_* [B][Hkv][T][Dh],
     win_count [B] int32 (all on the device)."""
-    import torch
+    torch = _torch or _load_torch()
     _need(win_k.dim() == 4 and win_k.is_contiguous() and win_v.is_contiguous(), "win_k/v [B][Hkv][W][Dh]")
     B, Hkv, W, Dh = win_k.shape
     _need(win_v.shape == win_k.shape and win_v.dtype == win_k.dtype, "win_v must match win_k")
@@ -428,44 +453,61 @@ def _decode_args(q, cme_k, cme_v, idx, k, win_k, win_v, win_count, new_k, new_v,
                  noalloc=False):
     """Checks shared by the decode wrappers; returns the C call's sizes and
     the (possibly allocated) out and workspace (none with noalloc)."""
-    import torch
-    _need(q.dim() == 3 and q.is_contiguous() and q.dtype == torch.float32, "q must be contiguous fp32 [B][Hq][Dh]")
-    B, Hq, Dh = q.shape
-    _need(cme_k.dim() == 4 and cme_k.is_contiguous() and cme_v.is_contiguous(), "cme_k/v [B][Hkv][N][Dh]")
-    _need(cme_k.shape[0] == B and cme_k.shape[3] == Dh and cme_v.shape == cme_k.shape, "pool shape")
-    _need(cme_v.dtype == cme_k.dtype, "cme_v dtype must match cme_k")
-    Hkv, N = cme_k.shape[1], cme_k.shape[2]
+    torch = _torch or _load_torch()
+    f32, i32 = torch.float32, torch.int32
+    qs, ps = q.shape, cme_k.shape
+    if not (len(qs) == 3 and q.dtype is f32 and q.is_contiguous()):
+        raise ValueError("q must be contiguous fp32 [B][Hq][Dh]")
+    B, Hq, Dh = qs
+    if not (len(ps) == 4 and cme_k.is_contiguous() and cme_v.is_contiguous()):
+        raise ValueError("cme_k/v [B][Hkv][N][Dh]")
+    _, Hkv, N, _ = ps
+    if not (ps[0] == B and ps[3] == Dh and cme_v.shape == ps):
+        raise ValueError("pool shape")
+    kv = cme_k.dtype
+    if cme_v.dtype is not kv:
+        raise ValueError("cme_v dtype must match cme_k")
     if W is None:
         W = 0 if win_k is None else win_k.shape[2]
     T = 0
+    wk = wv = wc = nk = nv = None
     if W > 0:
-        _need(win_k.shape == (B, Hkv, W, Dh) and win_v.shape == win_k.shape, "window shape")
-        _need(win_k.dtype == cme_k.dtype == win_v.dtype, "window dtype must match pool")
-        _need(win_k.is_contiguous() and win_v.is_contiguous(), "window must be contiguous")
-        _need(win_count is not None and win_count.shape == (B,) and win_count.dtype == torch.int32,
-              "win_count [B] int32")
+        if not (win_k.shape == (B, Hkv, W, Dh) and win_v.shape == win_k.shape):
+            raise ValueError("window shape")
+        if not (win_k.dtype is kv and win_v.dtype is kv):
+            raise ValueError("window dtype must match pool")
+        if not (win_k.is_contiguous() and win_v.is_contiguous()):
+            raise ValueError("window must be contiguous")
+        if not (win_count is not None and win_count.shape == (B,) and win_count.dtype is i32):
+            raise ValueError("win_count [B] int32")
         if new_k is not None:
-            _need(new_k.dim() == 4 and new_k.shape[:2] == (B, Hkv) and new_k.shape[3] == Dh,
-                  "new_k [B][Hkv][T][Dh]")
-            _need(new_v.shape == new_k.shape and new_k.dtype == new_v.dtype == cme_k.dtype, "new_k/v must match")
-            _need(new_k.is_contiguous() and new_v.is_contiguous(), "new_k/v must be contiguous")
-            T = int(new_k.shape[2])
-    if idx is not None:
-        _need(idx.shape == (B, k) and idx.dtype == torch.int32 and idx.is_contiguous(), "idx [B][k] int32")
-    if k_len is not None:
-        _need(k_len.shape == (B,) and k_len.dtype == torch.int32 and k_len.is_contiguous(), "k_len [B] int32")
+            ns = new_k.shape
+            if not (len(ns) == 4 and ns[0] == B and ns[1] == Hkv and ns[3] == Dh):
+                raise ValueError("new_k [B][Hkv][T][Dh]")
+            if not (new_v.shape == ns and new_k.dtype is kv and new_v.dtype is kv):
+                raise ValueError("new_k/v must match")
+            if not (new_k.is_contiguous() and new_v.is_contiguous()):
+                raise ValueError("new_k/v must be contiguous")
+            T = ns[2]
+    if idx is not None and not (idx.shape == (B, k) and idx.dtype is i32 and idx.is_contiguous()):
+        raise ValueError("idx [B][k] int32")
+    if k_len is not None and not (k_len.shape == (B,) and k_len.dtype is i32 and k_len.is_contiguous()):
+        raise ValueError("k_len [B] int32")
     if out is None:
-        out = torch.empty((B, Hq, Dh), dtype=torch.float32, device=q.device)
-    _need(out.shape == (B, Hq, Dh) and out.dtype == torch.float32 and out.is_contiguous(), "out [B][Hq][Dh] fp32")
+        out = torch.empty((B, Hq, Dh), dtype=f32, device=q.device)
+    elif not (out.shape == qs and out.dtype is f32 and out.is_contiguous()):
+        raise ValueError("out [B][Hq][Dh] fp32")
     ws_bytes = 0
     if not noalloc:
         if workspace is None:
             workspace = decode_workspace(B, Hq, Hkv, Dh, k, W, q.device)
         ws_bytes = workspace.numel() * workspace.element_size()
-    win = ((_ptr(win_k), _ptr(win_v), _ptr(win_count)) if W > 0 else (None, None, None))
-    new = ((_ptr(new_k), _ptr(new_v)) if W > 0 and new_k is not None else (None, None))
-    return dict(B=B, Hq=Hq, Hkv=Hkv, Dh=Dh, N=N, W=int(W), T=T, win=win, new=new, out=out, workspace=workspace,
-                ws_bytes=ws_bytes, dtype=_kv_dtype(cme_k))
+    if W > 0:
+        wk, wv, wc = _ptr(win_k), _ptr(win_v), _ptr(win_count)
+        if new_k is not None:
+            nk, nv = _ptr(new_k), _ptr(new_v)
+    return dict(B=B, Hq=Hq, Hkv=Hkv, Dh=Dh, N=N, W=int(W), T=T, win=(wk, wv, wc), new=(nk, nv), out=out,
+                workspace=workspace, ws_bytes=ws_bytes, dtype=_kv_dtype(cme_k))
 
 
 def cmc_two_tier_decode(q, cme_k, cme_v, idx, k: int, win_k, win_v, win_count, scale: float,
