@@ -28,8 +28,8 @@
 // Eq. 3 bits.  With a(i) the last passing position before i (-1 if none),
 // the floor keeps exactly the positions a(i) + m, a(i) + 2m, ... before the
 // next passing one, so kept(i) = pass(i) or (i - a(i)) mod m == 0.  a(i) is
-// a block-wide max-scan, the output slots a sum-scan; 8 positions per
-// thread per round, carried across rounds.
+// a block-wide max-scan, the output slots a sum-scan; 4 or 8 positions
+// per thread per round, carried across rounds.
 #include <limits.h>
 
 #include "device_common.hpp"
@@ -85,9 +85,9 @@ struct Lane16<uint16_t> {
     }
 };
 
-template <typename T, int G>
+template <typename T, int G, int TT>
 __global__ __launch_bounds__(256) void denoise_score_kernel(DenoiseParams p) {
-    constexpr int TT = kTokensPerWave, R = TT + G, VEC = Lane16<T>::N, P = kPasses, SPAN = kWave * VEC;
+    constexpr int R = TT + G, VEC = Lane16<T>::N, P = kPasses, SPAN = kWave * VEC;
     const int b = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nb = p.n_tokens ? clamp_tokens(p.n_tokens[b], p.n) : p.n;
@@ -443,7 +443,6 @@ __global__ __launch_bounds__(256, 2) void denoise_gram_wg_kernel(DenoiseParams p
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
-constexpr int kPerThread = 8;
 
 // Block-wide exclusive scans over thread order (sum and max), with the
 // block total / maximum returned through `total`.
@@ -490,7 +489,16 @@ __device__ __forceinline__ int block_excl_max(int v, int *s_w, int &total) {
     return lane > 0 ? max(base, prev_in_wave) : base;
 }
 
+// Bound by latency: the load of the Eq. 3 bytes, two block scans of six steps
+// and two barriers each, the stores.  Q words of 4 positions per thread: one
+// up to n = 4096 (every thread has a word), else two, which saves a round of
+// all that.  A thread's bytes move as words, and the remainder modulo m is
+// taken once and counted along: the call for one context of 3072 tokens 14.0
+// -> 13.1 us, 64 contexts 73.8 -> 72.8 us; with one word at n = 8000 19.7 ->
+// 20.6 us.
+template <int Q>
 __global__ __launch_bounds__(kSelThreads) void denoise_select_kernel(DenoiseParams p) {
+    constexpr int kPerThread = 4 * Q;
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
     const int nb = p.n_tokens ? clamp_tokens(p.n_tokens[b], p.n) : p.n;
@@ -498,50 +506,70 @@ __global__ __launch_bounds__(kSelThreads) void denoise_select_kernel(DenoisePara
     const uint8_t *pass = p.pass + (size_t)b * p.n;
     int32_t *idx = p.kept_idx + (size_t)b * p.n;
     __shared__ int s_w[kSelWaves];
+    const bool whole_words = ((size_t)b * p.n) % 4 == 0;  // the arrays themselves are 16-byte aligned
 
     int carry_last = -1, carry_count = 0;
     for (int r0 = 0; r0 < nb; r0 += kSelThreads * kPerThread) {
         const int j0 = r0 + tid * kPerThread;
-        uint32_t bits = 0;
+        // The thread's Eq. 3 bytes (0 or 1), 0 past the end: as words where
+        // they are aligned and whole.
+        uint32_t bytes[Q];
         int last = -1;
 #pragma unroll
-        for (int u = 0; u < kPerThread; ++u) {
-            const int i = j0 + u;
-            if (i < nb && pass[i]) {
-                bits |= 1u << u;
-                last = i;
+        for (int q = 0; q < Q; ++q) {
+            const int jq = j0 + 4 * q;
+            bytes[q] = 0;
+            if (whole_words && jq + 4 <= nb) {
+                bytes[q] = *reinterpret_cast<const uint32_t *>(pass + jq);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (jq + u < nb) bytes[q] |= (uint32_t)pass[jq + u] << (8 * u);
             }
+            if (bytes[q]) last = jq + (31 - __builtin_clz(bytes[q])) / 8;
         }
         int block_last;
         const int before = block_excl_max(last, s_w, block_last);
-        int a = max(carry_last, before);
-        uint32_t keep = 0;
-        int cnt = 0;
+        const int a = max(carry_last, before);
+        // (i - a) mod m for the thread's first position, then counted along.
+        uint32_t keep[Q];  // a byte per position
+        int r = m > 0 ? (j0 - a) % m : 1, cnt = 0;
 #pragma unroll
         for (int u = 0; u < kPerThread; ++u) {
-            const int i = j0 + u;
-            if (i < nb) {
-                const bool ps = (bits >> u) & 1u;
-                const bool k = ps || (m > 0 && (i - a) % m == 0);
-                if (ps) a = i;
-                if (k) {
-                    keep |= 1u << u;
-                    ++cnt;
-                }
+            if (u % 4 == 0) keep[u / 4] = 0;
+            const bool ps = (bytes[u / 4] >> (8 * (u % 4))) & 1u;
+            if (ps) r = 0;
+            if (j0 + u < nb && (ps || (m > 0 && r == 0))) {
+                keep[u / 4] |= 1u << (8 * (u % 4));
+                ++cnt;
             }
+            ++r;
+            if (r == m) r = 0;
         }
         int block_cnt;
         int o = carry_count + block_excl_sum(cnt, s_w, block_cnt);
 #pragma unroll
         for (int u = 0; u < kPerThread; ++u) {
             const int i = j0 + u;
-            if ((keep >> u) & 1u) {
+            if ((keep[u / 4] >> (8 * (u % 4))) & 1u) {
                 idx[o] = i;
                 if (p.chunk_offset && p.chunk_tokens > 0 && o % p.chunk_tokens == 0)
                     p.chunk_offset[(size_t)b * p.max_chunks + o / p.chunk_tokens] = i;
                 ++o;
             }
-            if (p.keep_out && i < nb) p.keep_out[(size_t)b * p.n + i] = (uint8_t)((keep >> u) & 1u);
+        }
+        if (p.keep_out) {
+            uint8_t *ko = p.keep_out + (size_t)b * p.n + j0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (whole_words && j0 + 4 * q + 4 <= nb) {
+                    *reinterpret_cast<uint32_t *>(ko + 4 * q) = keep[q];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (j0 + 4 * q + u < nb) ko[4 * q + u] = (uint8_t)((keep[q] >> (8 * u)) & 1u);
+                }
+            }
         }
         carry_last = max(carry_last, block_last);
         carry_count += block_cnt;
@@ -593,6 +621,24 @@ hipError_t launch_gram(const DenoiseParams &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Tokens per wave of the VALU kernel: kTokensPerWave, whose g halo rows are
+// the smaller share, or half as many while the waves of the whole batch do
+// not fill the chip (two per SIMD, 2048): each then streams half the rows and
+// reduces half the sums.  Calls at g = 3, H = 1280, whole / half: 3072 tokens
+// 13.1 / 11.6 us, 12288 tokens 20.2 / 18.8 us (18432 tokens at g = 4 stay
+// whole: 28.8 us).
+template <typename T, int G>
+void launch_score(const DenoiseParams &p, hipStream_t stream) {
+    constexpr int kHalf = kTokensPerWave > 1 ? kTokensPerWave / 2 : 1;
+    const bool few = (long long)p.B * p.n < 2048LL * kTokensPerWave;
+    const int per_wg = 4 * (few ? kHalf : kTokensPerWave);
+    int gx = (p.n + per_wg - 1) / per_wg;
+    if (CMC_DENOISE_WG_PER_SEQ > 0 && gx > CMC_DENOISE_WG_PER_SEQ) gx = CMC_DENOISE_WG_PER_SEQ;
+    const dim3 grid(gx, p.B);
+    if (few) denoise_score_kernel<T, G, kHalf><<<grid, 256, 0, stream>>>(p);
+    else denoise_score_kernel<T, G, kTokensPerWave><<<grid, 256, 0, stream>>>(p);
+}
+
 template <typename T>
 hipError_t launch_scores(const DenoiseParams &p, hipStream_t stream) {
     if (sizeof(T) == 2 && CMC_DENOISE_MFMA) {
@@ -604,14 +650,11 @@ hipError_t launch_scores(const DenoiseParams &p, hipStream_t stream) {
             default: return hipErrorInvalidValue;
         }
     }
-    int gx = (p.n + 4 * kTokensPerWave - 1) / (4 * kTokensPerWave);
-    if (CMC_DENOISE_WG_PER_SEQ > 0 && gx > CMC_DENOISE_WG_PER_SEQ) gx = CMC_DENOISE_WG_PER_SEQ;
-    dim3 grid(gx, p.B);
     switch (p.g) {
-        case 1: denoise_score_kernel<T, 1><<<grid, 256, 0, stream>>>(p); break;
-        case 2: denoise_score_kernel<T, 2><<<grid, 256, 0, stream>>>(p); break;
-        case 3: denoise_score_kernel<T, 3><<<grid, 256, 0, stream>>>(p); break;
-        case 4: denoise_score_kernel<T, 4><<<grid, 256, 0, stream>>>(p); break;
+        case 1: launch_score<T, 1>(p, stream); break;
+        case 2: launch_score<T, 2>(p, stream); break;
+        case 3: launch_score<T, 3>(p, stream); break;
+        case 4: launch_score<T, 4>(p, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -625,7 +668,8 @@ hipError_t launch_denoise(const DenoiseParams &p, bool bf16, hipStream_t stream)
         const hipError_t e = bf16 ? launch_scores<uint16_t>(p, stream) : launch_scores<float>(p, stream);
         if (e != hipSuccess) return e;
     }
-    denoise_select_kernel<<<p.B, kSelThreads, 0, stream>>>(p);
+    if (p.n <= 4 * kSelThreads) denoise_select_kernel<1><<<p.B, kSelThreads, 0, stream>>>(p);
+    else denoise_select_kernel<2><<<p.B, kSelThreads, 0, stream>>>(p);
     return hipGetLastError();
 }
 

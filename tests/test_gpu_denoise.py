@@ -86,6 +86,18 @@ def test_denoise_sizes(orc, dtype, n, H, n_tokens):
     _check_denoise(orc, emb, 3, 0.05, 16, n_tokens, chunk_tokens=256, what="sizes")
 
 
+@pytest.mark.parametrize("B,n", [(2, 4096), (2, 4097), (3, 4095), (4, 4096), (1, 8191), (2, 8192), (1, 8193), (3, 12289)])
+def test_denoise_dispatch_edges(orc, B, n):
+    """Both sides of the lines of the dispatch: 4096 positions (one word of
+    four per thread, then two), 16384 tokens in the batch (half, then whole
+    groups of tokens per wave), a second round of positions; widths of rows
+    that make the words unaligned, fp32, g = 4."""
+    rng = np.random.default_rng(n + B)
+    e = rng.standard_normal((B, n, 16)).astype(np.float32)
+    e[:, 1:] += 0.3 * e[:, :-1]
+    _check_denoise(orc, e, 4, 0.4, 5, [max(0, n - 3 * i) for i in range(B)], chunk_tokens=9, what="dispatch")
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_denoise_random_configs(orc, seed):
     """Seeded random batch, length, width, neighbourhood, threshold, floor,
