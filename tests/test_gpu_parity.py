@@ -353,7 +353,7 @@ def test_decode_step_fused(orc, dtype, Dh, G, t_new, W, fill):
     (64, 4, 1, 64, "f32", 30, 10, 0, 0),          # 256 pairs, no window
 ])
 def test_decode_wide_workgroups(orc, B, Hkv, G, Dh, dtype, N, k, W, fill):
-    """Batches with 192..256 (sequence, kv head) pairs run one 8-wave
+    """Batches with up to 256 (sequence, kv head) pairs run one 8-wave
     workgroup per pair; results match the oracle like every other plan."""
     _decode_case(orc, B=B, Hq=G * Hkv, Hkv=Hkv, Dh=Dh, N=N, k=k, W=W, fill=fill, dtype=dtype,
                  seed=B * Hkv + G + Dh, steps=3, fused=W > 0)
