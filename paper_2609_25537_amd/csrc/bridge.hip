@@ -405,6 +405,75 @@ __global__ __launch_bounds__(256) void bridge_norm_kernel(BridgeParams p) {
     }
 }
 
+// The same row by a whole workgroup, for calls whose rows are too few to fill
+// the chip with one wave each (see launch_norm): a quarter of the loads and of
+// the tanh evaluations per lane, and three block sums through LDS.
+template <int NV>
+__global__ __launch_bounds__(256) void bridge_norm_wg_kernel(BridgeParams p) {
+    __shared__ float s_sum[3][4];
+    const int tid = threadIdx.x, row = blockIdx.x;
+    float4 *y4 = reinterpret_cast<float4 *>(p.out + (size_t)row * p.Hd);
+    const float4 *g4 = reinterpret_cast<const float4 *>(p.ln_gamma);
+    const float4 *b4 = reinterpret_cast<const float4 *>(p.ln_beta);
+    const int n4 = p.Hd / 4;
+    // Every barrier is reached by the whole workgroup; each sum has a slot.
+    auto block_sum = [&](float v, int slot) {
+        v = lane_reduce<OpSum, 1, kWave>(v);
+        if ((tid & 63) == 0) s_sum[slot][tid >> 6] = v;
+        __syncthreads();
+        return (s_sum[slot][0] + s_sum[slot][1]) + (s_sum[slot][2] + s_sum[slot][3]);
+    };
+    float4 v[NV], g[NV], b[NV];
+    float s = 0.f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int c = min(tid + u * 256, n4 - 1);  // past the end: loaded, not used
+        v[u] = y4[c];
+        g[u] = g4[c];
+        b[u] = b4[c];
+    }
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+        if (tid + u * 256 < n4) s += (v[u].x + v[u].y) + (v[u].z + v[u].w);
+    const float mean = block_sum(s, 0) / (float)p.Hd;
+    float q = 0.f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        if (tid + u * 256 < n4) {
+            const float a = v[u].x - mean, e = v[u].y - mean, d = v[u].z - mean, f = v[u].w - mean;
+            q = fmaf(a, a, q);
+            q = fmaf(e, e, q);
+            q = fmaf(d, d, q);
+            q = fmaf(f, f, q);
+        }
+    }
+    const float var = block_sum(q, 1) / (float)p.Hd;
+    const float inv = 1.f / sqrtf(var + p.eps);
+    float nn = 0.f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        v[u] = float4{p.nu * tanh_cap(fmaf(g[u].x * (v[u].x - mean), inv, b[u].x)),
+                      p.nu * tanh_cap(fmaf(g[u].y * (v[u].y - mean), inv, b[u].y)),
+                      p.nu * tanh_cap(fmaf(g[u].z * (v[u].z - mean), inv, b[u].z)),
+                      p.nu * tanh_cap(fmaf(g[u].w * (v[u].w - mean), inv, b[u].w))};
+        if (tid + u * 256 < n4) {
+            nn = fmaf(v[u].x, v[u].x, nn);
+            nn = fmaf(v[u].y, v[u].y, nn);
+            nn = fmaf(v[u].z, v[u].z, nn);
+            nn = fmaf(v[u].w, v[u].w, nn);
+        }
+    }
+    const float nrm = sqrtf(block_sum(nn, 2));
+    const float scale = (nrm > 0.f && 2.f * p.nu < nrm) ? 2.f * p.nu / nrm : 1.f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int c = tid + u * 256;
+        if (c < n4)
+            st16_nt(&y4[c], make_uint4(__float_as_uint(v[u].x * scale), __float_as_uint(v[u].y * scale),
+                                       __float_as_uint(v[u].z * scale), __float_as_uint(v[u].w * scale)));
+    }
+}
+
 // Rows wider than 256 * 16: the same steps re-reading the row from cache.
 __global__ __launch_bounds__(256) void bridge_norm_wide_kernel(BridgeParams p) {
     const int lane = threadIdx.x & 63;
@@ -494,6 +563,16 @@ __global__ __launch_bounds__(256) void cme_norm_kernel(const uint16_t *h, int M,
 }
 
 hipError_t launch_norm(const BridgeParams &p, hipStream_t stream) {
+    // A workgroup per row below 2048 rows (2048 waves fill the chip with one
+    // row each).  Whole calls, Hc = 1280, F = Hd = 4096, wave / workgroup per
+    // row: 48 rows 47.3 / 39.5 us, 768 rows 89.3 / 85.5, 3072 rows 212.9 /
+    // 213.5, 16384 rows 884 / 899, 49152 rows 2539 / 2553.
+    if (p.M < 2048 && p.Hd <= 1024 * 4) {
+        if (p.Hd <= 1024) bridge_norm_wg_kernel<1><<<p.M, 256, 0, stream>>>(p);
+        else if (p.Hd <= 2048) bridge_norm_wg_kernel<2><<<p.M, 256, 0, stream>>>(p);
+        else bridge_norm_wg_kernel<4><<<p.M, 256, 0, stream>>>(p);
+        return hipGetLastError();
+    }
     const unsigned grid = (unsigned)((p.M + 3) / 4);
     if (p.Hd <= 256 * 4)
         bridge_norm_kernel<4><<<grid, 256, 0, stream>>>(p);

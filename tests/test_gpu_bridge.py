@@ -119,6 +119,17 @@ def test_bridge_tile_choice_edges(orc, M):
     _run(orc, h, _params(rng, 64, 1024, 256), nu=0.8, rows=rows, what="tile choice")
 
 
+@pytest.mark.parametrize("M,Hd", [(3, 1024), (5, 1152), (130, 2048), (7, 2176), (67, 4096), (2, 4224), (2047, 256),
+                                  (2048, 256)])
+def test_bridge_row_kernel_edges(orc, M, Hd):
+    """Widths around those of the row kernels' instantiations, and row
+    counts on both sides of the line between a workgroup and a wave per row."""
+    rng = np.random.default_rng(M + Hd)
+    h = wl.f32_to_bf16_bits(rng.standard_normal((M, 64)).astype(np.float32))
+    rows = sorted({0, M // 2, M - 1, *rng.integers(0, M, size=30).tolist()})
+    _run(orc, h, _params(rng, 64, 128, Hd), nu=0.8, rows=rows, what="row kernel")
+
+
 def test_bridge_more_tiles_than_cus(orc):
     """More 256 x 256 tiles than CUs (33 x 8 = 264 for the first layer), so
     workgroups of a persistent grid take several tiles; every row checked."""
