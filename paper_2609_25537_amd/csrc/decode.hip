@@ -52,6 +52,7 @@
 // Publication uses agent-coherent relaxed atomics plus a store-completion
 // wait instead of device-scope fences (see coherent_store2).  A head whose key
 // list is empty gets zeros.
+#include <float.h>
 #include <limits.h>
 
 #include <type_traits>
@@ -70,6 +71,11 @@ namespace {
 #endif
 
 constexpr float kLog2e = 1.4426950408889634f;
+
+// A running max before any key.  Finite, so that a key whose score is -inf
+// weighs exp2(-inf) = 0 also where no other key came before it (from -inf
+// the difference would be NaN, and with it the whole head).
+constexpr float kNoMax = -FLT_MAX;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -115,7 +121,7 @@ struct WaveState {
     __device__ __forceinline__ void init() {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            m[g] = -INFINITY;
+            m[g] = kNoMax;
             if (g < kLaneHeads<G>) l[g] = 0.f;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[g][i] = 0.f;
@@ -331,7 +337,14 @@ struct QOperand<uint16_t, DH, G> {
                 }
             }
         }
-        return kParts > 2 ? sum + rest : c;
+        if constexpr (kParts > 2) {
+            // An infinite key element: the large parts have q's signs and give
+            // the score; the small ones may differ in sign, so their sum is
+            // held finite (also where it is NaN).
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c[e] = sum[e] + __builtin_amdgcn_fmed3f(rest[e], -FLT_MAX, FLT_MAX);
+        }
+        return c;
     }
 };
 
@@ -482,6 +495,18 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
             }                                                                                        \
         }                                                                                            \
     } while (0)
+    // A phase without masks ends in copies of its last row: their values are
+    // zeroed, since an infinite one times p = 0 is NaN.
+#define CMC_TAIL(B0_, VR_)                                                                            \
+    do {                                                                                             \
+        if constexpr (!Rows::kMasked && (sizeof(T) == 4 || G > 4)) {                                 \
+            if ((B0_) + 16 > r1) {                                                                   \
+                _Pragma("unroll") for (int qq = 0; qq < 4; ++qq)                                     \
+                    if ((B0_) + 4 * qq + kq >= r1)                                                   \
+                        _Pragma("unroll") for (int j = 0; j < VW; ++j) VR_[qq][j] = make_uint4(0, 0, 0, 0); \
+            }                                                                                        \
+        }                                                                                            \
+    } while (0)
     // S = Q K^T by MFMA; online softmax rescaling the accumulators only when
     // a head's running max grows (wave-uniform: every lane row holds the same
     // scores); P V on the VALU.
@@ -503,7 +528,7 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
         _Pragma("unroll") for (int g = 0; g < G; ++g) {                                              \
             const float mb = mbs[g];                                                                 \
             if (mb > st.m[g]) {                                                                      \
-                if (st.m[g] != -INFINITY) { /* before the first valid key l and acc are 0 */         \
+                if (st.m[g] != kNoMax) { /* before the first valid key l and acc are 0 */            \
                     const float alpha = fast_exp2(st.m[g] - mb);                                     \
                     if constexpr (G > 4) st.l[g % NH] *= (g >= 4) == upper ? alpha : 1.f;            \
                     else st.l[g] *= alpha;                                                           \
@@ -515,7 +540,7 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
         _Pragma("unroll") for (int g = 0; g < NH; ++g) {                                             \
             const float ma = st.m[g], mb = st.m[(g + 4) % G];                                        \
             const float m = G > 4 && upper ? mb : ma;                                                \
-            /* a masked key weighs 0 (also before any valid key: m is -inf) */                       \
+            /* a masked key weighs 0 */                                                              \
             pk[g] = kval ? fast_exp2(c[g] - m) : 0.f;                                                \
             st.l[g] += pk[g];                                                                        \
         }                                                                                            \
@@ -593,6 +618,7 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
             CMC_LOAD(blk, kc, kvc, kr, vr);
             CMC_AFTER_FIRST_LOAD();
             CMC_KEYS(blk + BSTRIDE, kc, kvc);
+            CMC_TAIL(blk, vr);
             CMC_COMPUTE(blk, kr, vr);
         }
         return;
@@ -606,6 +632,7 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
     while (true) {
         int nb = blk + BSTRIDE;
         if (nb >= r1) {  // wave-uniform
+            CMC_TAIL(blk, vA);
             CMC_COMPUTE(blk, kA, vA);
             break;
         }
@@ -619,6 +646,7 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
         blk = nb;
         nb = blk + BSTRIDE;
         if (nb >= r1) {
+            CMC_TAIL(blk, vB);
             CMC_COMPUTE(blk, kB, vB);
             break;
         }
@@ -633,6 +661,7 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
     }
 #undef CMC_KEYS
 #undef CMC_LOAD
+#undef CMC_TAIL
 #undef CMC_COMPUTE
 #undef CMC_AFTER_FIRST_LOAD
 }
@@ -708,8 +737,8 @@ __device__ __forceinline__ float combine_waves(const float (&sm)[NW][G], const f
                                                const float (&sa)[NW][G][DH], int g, int d, float &num,
                                                float &den) {
     // Every LDS read issued before the first wait, and no branch on M: with
-    // no valid key in any wave (M = -inf) every weight is exp2(-inf) = 0
-    // against finite accumulators (zeros), so num = den = 0.
+    // no valid key in any wave (M = kNoMax) the weights are 1 against zeros, so
+    // num = den = 0.
     float mw[NW], lw[NW], aw[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -720,12 +749,11 @@ __device__ __forceinline__ float combine_waves(const float (&sm)[NW][G], const f
     float M = mw[0];
 #pragma unroll
     for (int w = 1; w < NW; ++w) M = fmaxf(M, mw[w]);
-    const float Mc = M == -INFINITY ? 0.f : M;
     num = 0.f;
     den = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float f = fast_exp2(mw[w] - Mc);
+        const float f = fast_exp2(mw[w] - M);
         num = fmaf(f, aw[w], num);
         den = fmaf(f, lw[w], den);
     }
@@ -942,12 +970,12 @@ __global__ __launch_bounds__(NW * kWave, (kMinWaves<T, DH, G>)) void decode_kern
                 mj[j] = v.x;
                 lj[j] = v.y;
             }
-            float M = -INFINITY;
+            float M = kNoMax;
 #pragma unroll
             for (int j = 0; j < kMB; ++j) M = fmaxf(M, mj[j]);
             for (int q = kMB; q < p.S; ++q) M = fmaxf(M, s_ml[(q * G + g) * 2]);
             float n0 = 0.f, n1 = 0.f, den = 0.f;
-            if (M != -INFINITY) {
+            if (M != kNoMax) {
 #pragma unroll
                 for (int j = 0; j < kMB; ++j) {
                     const bool in = j < p.S;

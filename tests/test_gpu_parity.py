@@ -371,6 +371,35 @@ def test_decode_plan_edges(orc, Dh, G, dtype, pairs):
                      steps=2, fused=fused)
 
 
+@pytest.mark.parametrize("Dh", [64, 128, 256])
+@pytest.mark.parametrize("dtype,G", [("f32", 1), ("f32", 2), ("f32", 4), ("f32", 8), ("bf16", 8)])
+@pytest.mark.parametrize("B,k,row", [(1, 17, 16), (1, 50, 0), (1, 50, 33), (1, 300, 299), (160, 40, 17)])
+def test_decode_infinite_elements(orc, dtype, G, Dh, B, k, row):
+    """A key whose score is -inf for every head weighs nothing, also where a
+    wave has no other key: the result is the oracle's without that row.  An
+    infinite value in a key list's last row reaches its own output dim only."""
+    rng = np.random.default_rng(k + row + Dh + G)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    cv = _bf16 if dtype == "bf16" else (lambda x: x)
+    pk, pv, q = f(B, 1, k, Dh), f(B, 1, k, Dh), f(B, G, Dh)
+    q[:, :, 5] = np.abs(q[:, :, 5]) + 0.5
+    pk[:, :, row, 5] = -np.inf
+    scale, tol = 1.0 / math.sqrt(Dh), tol_for(dtype)
+    say(f"infinite key {dtype} G={G} Dh={Dh} B={B} k={k} row={row}")
+    out = to_host(cmc.cmc_two_tier_decode(to_dev(q), to_dev(cv(pk)), to_dev(cv(pv)), None, k, None, None, None, scale))
+    keep = [j for j in range(k) if j != row]
+    ref = orc.two_tier_decode(q, cv(pk[:, :, keep]), cv(pv[:, :, keep]), None, k - 1, None, None, None, 0, scale)
+    assert np.isfinite(out).all() and max_abs(out, ref) <= tol
+
+    say(f"infinite value {dtype} G={G} Dh={Dh} B={B} k={k}")
+    pk[:, :, row, 5] = 0.0
+    ref = orc.two_tier_decode(q, cv(pk), cv(pv), None, k, None, None, None, 0, scale)
+    pv[:, :, k - 1, 3] = np.inf
+    out = to_host(cmc.cmc_two_tier_decode(to_dev(q), to_dev(cv(pk)), to_dev(cv(pv)), None, k, None, None, None, scale))
+    assert np.isposinf(out[:, :, 3]).all()
+    assert max_abs(np.delete(out, 3, 2), np.delete(ref, 3, 2)) <= tol
+
+
 def _random_decode_config(seed):
     """A seeded random decode configuration within the ABI's limits."""
     r = np.random.default_rng(seed)
