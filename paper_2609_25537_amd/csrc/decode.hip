@@ -761,10 +761,14 @@ __device__ __forceinline__ float combine_waves(const float (&sm)[NW][G], const f
 }
 
 // Waves per SIMD the compiler must leave registers for, where its own choice
-// would be one: eight heads (but not of 256, whose accumulators alone take
-// half of the registers) and 256-wide fp32 rows.
-template <typename T, int DH, int G>
-constexpr int kMinWaves = G * DH <= 1024 && (G > 4 || sizeof(T) * DH > 512) ? 2 : 1;
+// would be fewer: one for eight heads (but not of 256, whose accumulators
+// alone take half of the registers) and 256-wide fp32 rows, and two for the
+// 4-wave kernel of eight heads of 128 in bf16, which keeps one block of rows
+// in flight per wave and so lives on its waves (264 pairs, 6144 keys: 221 us
+// with two, 172 us with three).
+template <int NW, typename T, int DH, int G>
+constexpr int kMinWaves = NW == 4 && sizeof(T) == 2 && DH == 128 && G == 8 ? 3
+                          : G * DH <= 1024 && (G > 4 || sizeof(T) * DH > 512) ? 2 : 1;
 
 // The leading arguments are the fields the first K/V loads need (info packs
 // S, new_split, whether k_len is given, and T_new); they arrive in
@@ -772,7 +776,7 @@ constexpr int kMinWaves = G * DH <= 1024 && (G > 4 || sizeof(T) * DH > 512) ? 2 
 // loads never wait for the kernel-argument segment.  The rest of the
 // parameters come from `pm`.
 template <int NW, typename T, int DH, int G, bool IX>
-__global__ __launch_bounds__(NW * kWave, (kMinWaves<T, DH, G>)) void decode_kernel(const void *cme_k, const void *cme_v, void *win_k,
+__global__ __launch_bounds__(NW * kWave, (kMinWaves<NW, T, DH, G>)) void decode_kernel(const void *cme_k, const void *cme_v, void *win_k,
                                                             void *win_v, int k, int W, int N, int Hkv, int chunk,
                                                             int info, DecodeParams pm) {
     DecodeParams p = pm;
