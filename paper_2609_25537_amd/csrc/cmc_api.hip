@@ -66,29 +66,54 @@ cmc_status check_keys(const char *fn, cmc_dtype key_dtype, int D) {
 #endif
 namespace cmc {
 
-// Key-axis split plan.  The decode kernel keeps eight waves resident per CU
-// (two per SIMD), so about 2048 waves, 512 workgroups of 4, fill the 256 CUs
-// in one round; what the rules below avoid is a second round that is mostly
-// empty, and splits whose partials and merge cost more than they spread.
-// Launch times in us before / after, Hkv = 8 and 256 + 512 keys, G = 4, Dh =
-// 128 in bf16 unless said otherwise:
-//   - From 129 (sequence, kv head) pairs (168 with Dh = 64) to 256, one 8-wave
-//     workgroup each, no merge, instead of 4-wave splits: 136 pairs 21.8 /
-//     18.5, 184 pairs 26.7 / 18.7 (512 + 1024 keys: 30.1 / 29.0, 35.8 / 29.0;
-//     G = 8: 23.0 / 22.1, 26.6 / 22.7).  Dh = 64 moves half the bytes per key
-//     and only gains from 168 on: at 136 pairs 13.2 / 13.6, at 168 15.9 / 13.6.
-//   - Otherwise 4-wave workgroups, a pair cut into as many splits as fit one
-//     round, the appended rows' own split counted: 40 pairs 13.4 / 12.4, 96
-//     pairs 19.2 / 14.5, 128 pairs 21.4 / 16.4.  (Rounding up instead, and the
-//     appended rows' splits on top, made 640 workgroups of 128 pairs.)
-//   - From 257 to 367 pairs that leaves one workgroup per pair and up to half
-//     of the chip's slots empty, so the pairs are cut in two after all (264
-//     pairs of 512 + 1024 keys: 51.5 cut, 55.5 not; fp32, Dh = 64: 52 / 60);
-//     from 368 on one workgroup per pair is faster (384 pairs: 37.7 cut, 31.6
-//     not; 448 pairs 43.1 / 33.5).  The same from 129 to 167 pairs with Dh =
-//     64 (fp32 G = 1, 136 pairs: 27.5 cut in four, 31.6 cut in two).
-// Never below kGranule keys per split.
-DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W, bool append) {
+// Key-axis split plan.  The decode kernel keeps two 4-wave workgroups resident
+// per CU (one for eight heads of 256, whose registers fill a SIMD), so
+// `slots` = 512 (256) of them fill the 256 CUs in one round.  What the rules
+// avoid is a second round that is mostly empty, CUs without a workgroup while
+// the others walk long lists, and splits whose partials and merge cost more
+// than they spread.  Times in us of a launch that appends a row, by
+// (sequence, kv head) pairs and keys k + W; G = 4, Dh = 128 in bf16 unless
+// said otherwise.
+//   - Up to 128 pairs: as many splits as fit one round.  The appended rows get
+//     a split of their own, so that no workgroup walks ring rows and appended
+//     rows one after the other, where the granule leaves a slot free for it,
+//     where the splits are many, or where the rows are (more than
+//     kFewAppendedRows); else the last split takes them.  (Workgroups are dealt to the XCDs in
+//     turn: every fourth or eighth of them with a single key leaves two of the
+//     eight XCDs, or one, idle.)  128 pairs as 3 splits and one / as 4: 768
+//     keys 18.1 / 16.9, 6144 keys 75.0 / 70.8; fp32, Dh = 64, G = 1, 768 keys
+//     15.1 / 13.7; 64 pairs as 7 and one / as 8, 1536 keys 17.5 / 16.0; but 24
+//     pairs, 1536 keys, as 12 and one / as 12: 13.2 / 13.7.  Eight heads of
+//     256, 64 pairs, 768 keys: 39.5 in 512 workgroups, 30.4 in 256; 128
+//     pairs, 6144 keys 248 / 184.
+//   - 129 to 170 pairs: three splits, which still fit one round, or one 8-wave
+//     workgroup per pair (4 waves where 8 are not built), without a merge but
+//     on 129 .. 170 of the CUs.  152 pairs, three splits / one workgroup: 200
+//     keys 13.2 / 11.5, 400 keys 15.3 / 14.7, 768 keys 18.6 / 19.5, 1536 keys
+//     27.3 / 30.2, 6144 keys 82.1 / 96.6; Dh = 64, 6144 keys, 168 pairs 52.4 /
+//     69.8; Dh = 256, G = 4, 768 keys, 168 pairs 32.7 / 32.6, 6144 keys 169 /
+//     188; the round is full at 170 pairs, G = 1, 520 keys 14.0 / 13.3.  G = 8 shares more work per key and gains later: 168 pairs, 768 keys
+//     24.5 / 23.8, 6144 keys 97 / 118; at Dh = 256, where three splits are two
+//     rounds, 168 pairs, 1536 keys 92.4 / 89.9, 3072 keys 145 / 162 (without
+//     appended rows from 512 keys on: fp32, 136 pairs, 768 keys 79 / 89).
+//   - 171 to 256 pairs: one workgroup per pair (184 pairs, 768 keys 19.6, cut
+//     in two 22.6; 6144 keys 99.2 / 114).
+//   - From 257 to 367 pairs that leaves up to half of the slots empty, so the
+//     pairs are cut in two after all (264 pairs of 1536 keys: 51.5 cut, 55.5
+//     not; fp32, Dh = 64: 52 / 60), but not short lists (320 pairs of 120
+//     keys: 19.0 cut, 12.4 not, 400 keys 28.4 / 22.2; fp32, 400 keys 42.2 /
+//     37.7).
+//   - From 368 on one workgroup per pair is faster (384 pairs of 768 keys: 37.7
+//     cut, 31.6 not; 448 pairs 43.1 / 33.5), but up to 384 pairs, where two
+//     splits still spread evenly over the CUs, not on long lists (368 pairs
+//     without an appended split: 768 keys 39.7 cut, 32.7 not; 3072 keys 98.8 /
+//     110, 6144 keys 178 / 211; Dh = 64, 3072 keys 60.6 / 70.7; Dh = 256, G =
+//     1, 1536 keys 106 / 110).
+// Never below kGranule keys per split.  The element size of K/V does not
+// enter: the workspace query does not know it.  Eight heads of 256 reserve the
+// partials of 512 workgroups all the same, so that the workspace's size and the
+// sizes that the fixed scratch refuses do not hang on the kernel's registers.
+DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W, int T_new) {
     constexpr long long kTargetWG = CMC_DECODE_TARGET_WG;
     constexpr long long kGranule = CMC_DECODE_GRANULE;
     // The merge stages S*G*2 floats in the kernel's LDS; one split more is
@@ -98,33 +123,51 @@ DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W, bool append
     const long long L = (long long)k + W;
     const long long pairs = (long long)B * Hkv;
     if (L <= 0 || pairs <= 0) return pl;
-    append = append && W > 0;
+    const bool append = T_new > 0 && W > 0;
     const int G = Hq / Hkv;
-    const long long wide_min = Dh >= 128 ? 129 : 168;
-    long long S, chunk;
-    if (pairs >= wide_min && pairs <= 256 && decode_waves_ok(8, G, Dh)) {
+    const bool one_per_cu = G * Dh > 1024;
+    const long long slots = one_per_cu ? kTargetWG / 2 : kTargetWG;
+    const auto cut = [&](long long splits, long long &chunk) {
+        chunk = std::max((L + splits - 1) / splits, (L + kMaxSplits - 1) / kMaxSplits);
+        chunk = ((chunk + kGranule - 1) / kGranule) * kGranule;
+        return (L + chunk - 1) / chunk;
+    };
+    long long target = 1, chunk = L;  // target: splits
+    bool own = false;                 // the appended rows get a split of their own
+    if (pairs <= 128) {
+        target = std::max(1LL, slots / pairs);
+        const long long fits = cut(target, chunk);
+        own = append && (fits < target || (T_new > kFewAppendedRows && target > 2) ||
+                         (target > 8 && cut(target - 1, chunk) + 1 >= fits));
+        if (own && fits == target) --target;
+    } else if (pairs <= 170) {
+        const long long from = G < 8 ? (pairs <= 168 ? 512 : 1536) : Dh < 256 ? 1536 : append ? 3072 : 512;
+        target = L >= from ? 3 : 1;
+    } else if (pairs > 256 && pairs < 368) {
+        target = L >= 512 ? 2 : 1;
+        own = append;
+    } else if (pairs >= 368 && pairs <= 384 && !one_per_cu) {
+        target = L * std::max(Dh, 128) >= 3072 * 128 ? 2 : 1;
+    }
+    long long S = 1;
+    if (target == 1 && pairs > 128 && pairs <= 256 && decode_waves_ok(8, G, Dh)) {
         pl.waves = 8;
-        S = 1;
         chunk = L;
     } else {
-        const bool round_up = (pairs > 256 && pairs < 368) || (Dh == 64 && pairs > 128 && pairs < wide_min);
-        const long long s_target = round_up ? (kTargetWG + pairs - 1) / pairs
-                                            : std::max(1LL, kTargetWG / pairs - (append ? 1 : 0));
-        chunk = (L + s_target - 1) / s_target;
-        chunk = std::max(chunk, (L + kMaxSplits - 1) / kMaxSplits);
-        chunk = ((chunk + kGranule - 1) / kGranule) * kGranule;
-        S = (L + chunk - 1) / chunk;
+        S = cut(target, chunk);
     }
     pl.S = (int)S;
     pl.chunk = (int)chunk;
-    // A split plan merges partials anyway: the rows appended in a call then
-    // get a split of their own, so no workgroup handles ring rows and
-    // appended rows one after the other.
-    pl.own_append = S > 1 && append;
-    const long long Sa = pl.own_append ? S + 1 : S;
+    pl.own_append = S > 1 && own;
+    long long parts = pl.own_append ? S + 1 : S;
+    if (one_per_cu && pairs <= 170) {
+        long long c;
+        const long long S512 = cut(std::max(1LL, kTargetWG / pairs - (append ? 1 : 0)), c);
+        parts = std::max(parts, S512 > 1 && append ? S512 + 1 : S512);
+    }
     pl.counter_bytes = align256((size_t)(B + pairs) * sizeof(unsigned));
-    pl.ml_bytes = Sa > 1 ? align256((size_t)(pairs * Sa * G * 2) * sizeof(float)) : 0;
-    pl.acc_bytes = Sa > 1 ? align256((size_t)(pairs * Sa * G * Dh) * sizeof(float)) : 0;
+    pl.ml_bytes = parts > 1 ? align256((size_t)(pairs * parts * G * 2) * sizeof(float)) : 0;
+    pl.acc_bytes = parts > 1 ? align256((size_t)(pairs * parts * G * Dh) * sizeof(float)) : 0;
     pl.total = pl.counter_bytes + pl.ml_bytes + pl.acc_bytes;
     return pl;
 }
@@ -401,8 +444,10 @@ cmc_status cmc_gather_tier1(const void *cme_k, const void *cme_v, cmc_dtype kv_d
 
 size_t cmc_decode_workspace_bytes(int B, int Hq, int Hkv, int Dh, int k, int W) {
     if (B < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || k < 0 || W < 0 || !supported_dh(Dh)) return 0;
-    return std::max(cmc::plan_decode(B, Hq, Hkv, Dh, k, W, false).total,
-                    cmc::plan_decode(B, Hq, Hkv, Dh, k, W, true).total);
+    size_t total = 0;
+    for (const int T_new : {0, 1, INT_MAX})
+        total = std::max(total, cmc::plan_decode(B, Hq, Hkv, Dh, k, W, T_new).total);
+    return total;
 }
 
 }  // extern "C"
@@ -503,7 +548,7 @@ cmc_status decode_impl(const char *fn, const float *q, const void *cme_k, const 
         misaligned(win_v) || misaligned(win_count) || misaligned(out) || misaligned(workspace) ||
         misaligned(new_k) || misaligned(new_v))
         return fail(CMC_ERR_UNSUPPORTED, "%s: every pointer must be 16-byte aligned", fn);
-    const cmc::DecodePlan pl = cmc::plan_decode(B, Hq, Hkv, Dh, k, W, T_new > 0);
+    const cmc::DecodePlan pl = cmc::plan_decode(B, Hq, Hkv, Dh, k, W, T_new);
     char *counters, *partials;
     if (noalloc) {
         const size_t nctr = ((size_t)B + (size_t)B * Hkv) * sizeof(unsigned);

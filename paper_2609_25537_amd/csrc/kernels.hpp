@@ -41,16 +41,20 @@ struct DecodeParams {
 // Rows one decode call may append (the launch packs T_new into 16 bits).
 constexpr int kMaxAppendRows = 65535;
 
+// Appended rows that the last split always takes on besides its own, where
+// they get no split of their own (see plan_decode).
+constexpr int kFewAppendedRows = 16;
+
 // Key-axis split plan; depends only on sizes and on whether the call appends
-// rows, so the workspace query (the larger of the two plans) and the launch
-// agree.  Workspace layout: [sequence counters | pair counters] (zero between
+// no rows, a few or many, so the workspace query (the largest of the three
+// plans) and the launch agree.  Workspace layout: [sequence counters | pair counters] (zero between
 // calls), then the per-split partials.
 struct DecodePlan {
     int S = 0, chunk = 0, waves = 4;  // S splits over the k + W rows
     bool own_append = false;          // one more split takes the appended rows
     size_t counter_bytes = 0, ml_bytes = 0, acc_bytes = 0, total = 0;
 };
-DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W, bool append);
+DecodePlan plan_decode(int B, int Hq, int Hkv, int Dh, int k, int W, int T_new);
 
 hipError_t launch_two_tier_decode(const DecodeParams &p, bool bf16, int G, int Dh, hipStream_t stream);
 float decode_qscale(float scale);

@@ -334,6 +334,34 @@ def test_gather_empty_ok():
     assert _gather(B=0) == cmc.CMC_OK and _gather(k=0) == cmc.CMC_OK
 
 
+def _splits(pairs, G, Dh, k, W):
+    """Splits per (sequence, kv head) pair whose partials (m, l and Dh sums per
+    head) the workspace reserves (0: none)."""
+    pad = lambda n: -(-n // 256) * 256
+    total = cmc.cmc_decode_workspace_bytes(pairs, G, 1, Dh, k, W) - pad(8 * pairs)
+    for s in range(2, 130):
+        if total == pad(8 * pairs * s * G) + pad(4 * pairs * s * G * Dh):
+            return s
+    assert total == 0
+    return 0
+
+
+@pytest.mark.parametrize("pairs,G,Dh,k,W,splits", [
+    # 129 .. 170 pairs: one workgroup per pair leaves 86 to 127 CUs idle while the others walk a long list
+    (129, 4, 128, 2048, 4096, 3), (136, 1, 256, 512, 1024, 3), (168, 8, 128, 2048, 4096, 3), (168, 4, 64, 2048, 4096, 3),
+    (129, 4, 128, 200, 311, 0), (168, 8, 128, 500, 1035, 0), (170, 4, 64, 512, 1024, 3), (170, 4, 64, 512, 1023, 0), (171, 4, 128, 2048, 4096, 0),
+    # 257 .. 367: cut in two, but not short lists; 368 .. 384: only long ones
+    (320, 4, 128, 200, 311, 0), (320, 4, 128, 200, 312, 3),
+    (368, 4, 128, 1024, 2048, 2), (384, 4, 64, 2048, 4096, 2), (385, 4, 128, 2048, 4096, 0), (368, 4, 128, 1000, 2000, 0),
+    # up to 128: as many as fit one round
+    (128, 4, 128, 256, 512, 4), (8, 4, 128, 256, 512, 13),
+])
+def test_decode_plan_by_work(pairs, G, Dh, k, W, splits):
+    """The split plan weighs pairs against list length, seen through the
+    partials that the workspace reserves."""
+    assert _splits(pairs, G, Dh, k, W) == splits
+
+
 def _noalloc(**kw):
     a = dict(q=FAKE, ck=FAKE, cv=FAKE, idx=FAKE, k=4, wk=FAKE, wv=FAKE, wc=FAKE, W=8, nk=FAKE, nv=FAKE, T=1,
              dt=cmc.CMC_BF16, B=1, Hq=8, Hkv=2, Dh=128, N=16, scale=0.1, out=FAKE, s=None)

@@ -400,6 +400,43 @@ def test_decode_infinite_elements(orc, dtype, G, Dh, B, k, row):
     assert max_abs(np.delete(out, 3, 2), np.delete(ref, 3, 2)) <= tol
 
 
+@pytest.mark.parametrize("Dh,G,dtype", [(128, 4, "bf16"), (64, 1, "f32"), (128, 8, "bf16"), (256, 8, "f32"), (256, 2, "bf16")])
+@pytest.mark.parametrize("pairs,L,t_new", [
+    (32, 300, 1), (103, 500, 16), (103, 500, 17), (128, 261, 1), (128, 261, 40),  # up to four splits: appended rows in the last or their own
+    (129, 511, 1), (129, 512, 40), (168, 520, 1), (170, 1536, 1), (171, 1536, 1), (150, 3072, 2),  # three splits, or one workgroup
+    (300, 511, 1), (300, 520, 40),  # cut in two, or not
+    (368, 1535, 1), (368, 1537, 1), (384, 3072, 1), (385, 3072, 1),                # long lists cut in two, not past 384
+])
+def test_decode_plan_by_work(orc, Dh, G, dtype, pairs, L, t_new):
+    """Both sides of the lines that the split plan draws by list length and
+    by appended rows, k_len = 0 among the sequences: appended rows that go to
+    the last of several splits reach ring, count and output.  Every 37th pair
+    is checked against the oracle, ring and count in full."""
+    rng = np.random.default_rng(pairs + L + t_new + Dh)
+    W = min(200, L - 1)
+    k, B, fill = L - W, pairs, W - 3
+    f = lambda *s: rng.standard_normal(s, dtype=np.float32)
+    cv = _bf16 if dtype == "bf16" else (lambda x: x)
+    pk, pv = f(1, 1, k, Dh), f(1, 1, k, Dh)  # one pool, shifted per sequence through the index list
+    wk, wv, nk, nv, q = cv(f(B, 1, W, Dh)), cv(f(B, 1, W, Dh)), cv(f(B, 1, t_new, Dh)), cv(f(B, 1, t_new, Dh)), f(B, G, Dh)
+    idx = np.ascontiguousarray((np.arange(k)[None] + 7 * np.arange(B)[:, None]) % k).astype(np.int32)
+    k_len = rng.integers(0, k + 1, B).astype(np.int32)
+    k_len[:3] = 0, 1, k
+    cnt = np.full((B,), fill, np.int32)
+    scale = 1.0 / math.sqrt(Dh)
+    say(f"plan {dtype} Dh={Dh} G={G} pairs={pairs} L={L} T={t_new}")
+    dpk, dpv = (to_dev(cv(x)).expand(B, 1, k, Dh).contiguous() for x in (pk, pv))
+    dwk, dwv, dc = to_dev(wk), to_dev(wv), to_dev(cnt)
+    out = to_host(cmc.cmc_decode_step_ragged(to_dev(q), dpk, dpv, to_dev(idx), to_dev(k_len), k, dwk, dwv, dc, to_dev(nk),
+                                             to_dev(nv), scale))
+    orc.window_append(wk, wv, cnt, nk, nv)
+    assert _same_bits(to_host(dwk), wk) and _same_bits(to_host(dwv), wv) and (to_host(dc) == cnt).all()
+    b = np.array(sorted({0, 1, 2, B - 1, *range(3, B, 37)}))
+    ref = orc.two_tier_decode_ragged(q[b], np.repeat(cv(pk), len(b), 0), np.repeat(cv(pv), len(b), 0), idx[b], k_len[b], k,
+                                     wk[b], wv[b], cnt[b], W, scale)
+    assert max_abs(out[b], ref) <= tol_for(dtype)
+
+
 def _random_decode_config(seed):
     """A seeded random decode configuration within the ABI's limits."""
     r = np.random.default_rng(seed)
