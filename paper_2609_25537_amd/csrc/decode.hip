@@ -91,6 +91,13 @@ __device__ __forceinline__ void wave_lds_sync() { asm volatile("" ::: "memory");
 // softmax weight below 2^-126 contributes nothing at fp32 precision anyway).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Whether softmax weights below 2^-126 are kept (as the library's exp2f gives
+// them; times a large value they count) instead of taken as 0.  A lane that
+// holds one takes a branch.  24 ragged sequences of 64/8 heads 35.1 -> 35.8
+// us; an fp32 step is as before.
+template <typename T, int G>
+constexpr bool kSmallWeights = sizeof(T) == 4 || G > 4;
+
 // 16-byte load; NT marks it non-temporal.  The MFMA path loads its V rows
 // that way and its K rows with ordinary loads.  Launch times, with the
 // Mistral-shaped batch rotated over 8 copies so that nothing is reused from
@@ -409,15 +416,29 @@ struct QOperand<float, DH, G> {
             } else {
                 a = x[kDot ? 0 : i];
             }
+            // Short runs, so that no partial sum is rounded often, over two
+            // accumulators where the registers are short, else four.  Output
+            // error against 64 bits (140 pairs, 300 keys) with runs of four
+            // chunks, and one of 16 for four heads of 256 / now: Dh = 64, G =
+            // 4 1.66e-7 / 1.61e-7, G = 8 1.67e-7 / 1.60e-7; Dh = 128, G = 8
+            // 1.72e-7 / 1.66e-7; Dh = 256, G = 4 2.25e-7 / 1.83e-7 (the lane
+            // sums that this walk replaced: 1.52e-7, 1.52e-7, 1.63e-7,
+            // 1.75e-7).  Times are the same but for four heads of 256: 136
+            // pairs of 120 keys 24.4 / 28.1 us, 24 pairs of 768 keys 22.6 /
+            // 23.4, 184 pairs of 3072 keys 258 / 265.
+            constexpr bool kTwo = DH > 128 && G == 4;
+            constexpr int kRun = DH <= 128 || kTwo ? 2 : 4;
             c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, __uint_as_float(kr[i].x), c, 0, 0, 0);
             c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, __uint_as_float(kr[i].y), c1, 0, 0, 0);
-            c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c2, 0, 0, 0);
-            c3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(kr[i].w), c3, 0, 0, 0);
-            // runs of four chunks, so that no partial sum is rounded often (one
-            // run where the registers are short)
-            constexpr int kRun = DH > 128 && G == 4 ? kChunks : 4;
+            if constexpr (kTwo) {
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c, 0, 0, 0);
+                c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(kr[i].w), c1, 0, 0, 0);
+            } else {
+                c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c2, 0, 0, 0);
+                c3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(kr[i].w), c3, 0, 0, 0);
+            }
             if (i % kRun == kRun - 1) {
-                sum = sum + ((c + c1) + (c2 + c3));
+                sum = sum + (kTwo ? c + c1 : (c + c1) + (c2 + c3));
                 c = c1 = c2 = c3 = floatx4{0.f, 0.f, 0.f, 0.f};
             }
         }
@@ -529,7 +550,8 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
             const float mb = mbs[g];                                                                 \
             if (mb > st.m[g]) {                                                                      \
                 if (st.m[g] != kNoMax) { /* before the first valid key l and acc are 0 */            \
-                    const float alpha = fast_exp2(st.m[g] - mb);                                     \
+                    const float d = st.m[g] - mb;                                                    \
+                    const float alpha = kSmallWeights<T, G> ? exp2f(d) : fast_exp2(d);               \
                     if constexpr (G > 4) st.l[g % NH] *= (g >= 4) == upper ? alpha : 1.f;            \
                     else st.l[g] *= alpha;                                                           \
                     _Pragma("unroll") for (int i = 0; i < VD; ++i) st.acc[g][i] *= alpha;            \
@@ -537,13 +559,21 @@ __device__ __forceinline__ void mfma_phase(const DecodeParams &p, int b, int kvh
                 st.m[g] = mb;                                                                        \
             }                                                                                        \
         }                                                                                            \
+        float xs[NH], least = 0.f;                                                                   \
         _Pragma("unroll") for (int g = 0; g < NH; ++g) {                                             \
             const float ma = st.m[g], mb = st.m[(g + 4) % G];                                        \
             const float m = G > 4 && upper ? mb : ma;                                                \
+            xs[g] = c[g] - m;                                                                        \
             /* a masked key weighs 0 */                                                              \
-            pk[g] = kval ? fast_exp2(c[g] - m) : 0.f;                                                \
-            st.l[g] += pk[g];                                                                        \
+            pk[g] = kval ? fast_exp2(xs[g]) : 0.f;                                                   \
+            if constexpr (kSmallWeights<T, G>) least = fminf(least, xs[g]);                          \
         }                                                                                            \
+        if constexpr (kSmallWeights<T, G>) {                                                         \
+            if (kval && least < -126.f) { /* rare */                                                 \
+                _Pragma("unroll") for (int g = 0; g < NH; ++g) pk[g] = exp2f(xs[g]);                 \
+            }                                                                                        \
+        }                                                                                            \
+        _Pragma("unroll") for (int g = 0; g < NH; ++g) st.l[g] += pk[g];                             \
         if (q4 < G / NH) {                                                                           \
             _Pragma("unroll") for (int g = 0; g < NH; ++g) s_p[r16 * G + q4 * NH + g] = pk[g];      \
         }                                                                                            \

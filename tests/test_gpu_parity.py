@@ -437,6 +437,52 @@ def test_decode_plan_by_work(orc, Dh, G, dtype, pairs, L, t_new):
     assert max_abs(out[b], ref) <= tol_for(dtype)
 
 
+@pytest.mark.parametrize("Dh", [64, 128, 256])
+@pytest.mark.parametrize("dtype,G", [("f32", 1), ("f32", 2), ("f32", 4), ("f32", 8), ("bf16", 8)])
+def test_decode_small_weights(orc, dtype, G, Dh):
+    """Softmax weights of about 2^-130 count when the value is large: the
+    first of ten keys (one wave's) takes all of the weight but has the value
+    0, the others 1.5 * 2^120.  The weight is subnormal (2^-149 steps: 2^-20
+    of it), its score (130 in log2 units) off by a few rounding steps of
+    2^-17."""
+    cv = _bf16 if dtype == "bf16" else (lambda x: x)
+    q, k, v = np.zeros((1, G, Dh), np.float32), np.zeros((1, 1, 10, Dh), np.float32), np.zeros((1, 1, 10, Dh), np.float32)
+    q[:, :, 7] = 1.0
+    k[0, 0, 1:, 7] = -130.0
+    v[0, 0, 1:] = 1.5 * 2.0 ** 120
+    scale = math.log(2.0)
+    say(f"small weights {dtype} G={G} Dh={Dh}")
+    out = to_host(cmc.cmc_two_tier_decode(to_dev(q), to_dev(cv(k)), to_dev(cv(v)), None, 10, None, None, None, scale))
+    ref = orc.two_tier_decode(q, cv(k), cv(v), None, 10, None, None, None, 0, scale)
+    assert ref.min() > 0.01 and (np.abs(out - ref) <= ref * (2.0 ** -20 + 4 * 2.0 ** -17)).all()
+
+
+def _rel(a, ref):
+    return float(np.linalg.norm(a.astype(np.float64) - ref) / np.linalg.norm(ref))
+
+
+@pytest.mark.parametrize("Dh", [64, 128, 256])
+@pytest.mark.parametrize("dtype,G", [("bf16", 1), ("bf16", 2), ("bf16", 4), ("bf16", 8), ("f32", 1), ("f32", 2), ("f32", 4),
+                                     ("f32", 8)])
+@pytest.mark.parametrize("B,k", [(3, 48), (2, 147), (140, 40), (140, 600), (200, 90)])
+def test_decode_error_against_64_bits(orc, dtype, G, Dh, B, k):
+    """Relative error (2-norm) of the 4- and 8-wave kernels, whole and split
+    lists, random q, K, V: fp32 throughout (fp32 K/V, and bf16 K/V with eight
+    heads, q in three bf16 parts) 1.1e-7 to 2.3e-7 seen, 3e-7 allowed; q in two
+    bf16 parts 1.9e-6 to 2.8e-6 seen, 4e-6 allowed (its rounding alone is up
+    to 2^-18 per product; without the second part it is 1e-3, and with two
+    parts eight heads would show 2e-6)."""
+    rng = np.random.default_rng(B * k + G + Dh)
+    cv = _bf16 if dtype == "bf16" else (lambda x: x)
+    q, pk, pv = (rng.standard_normal(s, dtype=np.float32) for s in ((B, G, Dh), (B, 1, k, Dh), (B, 1, k, Dh)))
+    scale = 1.0 / math.sqrt(Dh)
+    say(f"error {dtype} G={G} Dh={Dh} B={B} k={k}")
+    out = to_host(cmc.cmc_two_tier_decode(to_dev(q), to_dev(cv(pk)), to_dev(cv(pv)), None, k, None, None, None, scale))
+    b = slice(0, min(B, 40))
+    ref = orc.two_tier_decode(q[b], cv(pk[b]), cv(pv[b]), None, k, None, None, None, 0, scale)
+    assert _rel(out[b], ref) <= (3e-7 if dtype == "f32" or G == 8 else 4e-6)
+
+
 def _random_decode_config(seed):
     """A seeded random decode configuration within the ABI's limits."""
     r = np.random.default_rng(seed)
