@@ -100,8 +100,9 @@ def _params(rng, Hc, F, Hd, gamma_scale=1.0):
     (40, 64, 256, 256), (513, 64, 512, 256), (1000, 192, 768, 512),
 ])
 def test_bridge_shapes(orc, M, Hc, F, Hd):
-    """Tile edges: M not a multiple of 128 or 256, several N and K tiles,
-    and K of two 32-wide slices (fewer slices than the pipeline's stages)."""
+    """Small calls, which run on 64 x 64 tiles: M not a multiple of 64,
+    several N and K tiles, and K of one 64-wide slice (fewer slices than the
+    pipeline's stages)."""
     rng = np.random.default_rng(M + Hc + F + Hd)
     h = wl.f32_to_bf16_bits(rng.standard_normal((M, Hc)).astype(np.float32))
     _run(orc, h, _params(rng, Hc, F, Hd), nu=0.8, what="shapes")
@@ -119,6 +120,21 @@ def test_bridge_tile_choice_edges(orc, M):
     _run(orc, h, _params(rng, 64, 1024, 256), nu=0.8, rows=rows, what="tile choice")
 
 
+@pytest.mark.parametrize("M,Hc,F,Hd", [
+    (12289, 192, 1280, 1024),  # 256 x 256 tiles for both layers: 3 and 20 slices of 64
+    (12289, 64, 1152, 1024),   # 128 x 128 (2 slices of 32), then 256 x 256 (18 slices)
+    (6017, 320, 1152, 1152),   # 128 x 128 for both: 10 and 36 slices of 32
+    (6017, 64, 1152, 1152),
+])
+def test_bridge_large_tiles(orc, M, Hc, F, Hd):
+    """Both large tiles over one, an odd and many slices of K, with both
+    epilogues, and one row in the last tile of each layer."""
+    rng = np.random.default_rng(M + Hc + F)
+    h = wl.f32_to_bf16_bits(rng.standard_normal((M, Hc), dtype=np.float32))
+    rows = sorted({0, 127, 128, 255, 256, M - 257, M - 130, M - 129, M - 2, M - 1, *rng.integers(0, M, size=40).tolist()})
+    _run(orc, h, _params(rng, Hc, F, Hd), nu=0.8, rows=rows, what="large tiles")
+
+
 @pytest.mark.parametrize("M,Hd", [(3, 1024), (5, 1152), (130, 2048), (7, 2176), (67, 4096), (2, 4224), (2047, 256),
                                   (2048, 256)])
 def test_bridge_row_kernel_edges(orc, M, Hd):
@@ -131,8 +147,9 @@ def test_bridge_row_kernel_edges(orc, M, Hd):
 
 
 def test_bridge_more_tiles_than_cus(orc):
-    """More 256 x 256 tiles than CUs (33 x 8 = 264 for the first layer), so
-    workgroups of a persistent grid take several tiles; every row checked."""
+    """More 256 x 256 tiles than CUs (33 x 8 = 264 for the first layer; the
+    second runs on 64 x 64 tiles), so a second round of workgroups; every row
+    checked."""
     rng = np.random.default_rng(8)
     M, Hc, F, Hd = 8192 + 77, 64, 2048, 512
     h = wl.f32_to_bf16_bits(rng.standard_normal((M, Hc)).astype(np.float32))

@@ -115,7 +115,7 @@ def test_decode_pass_graph(B, Hq, Hkv, Dh, N, D, k, W, fill):
 def test_bridge_graph():
     say("graph memory bridge")
     rng = np.random.default_rng(11)
-    M, Hc, F, Hd = 600, 128, 512, 256  # 256 x 256 tiles for both layers
+    M, Hc, F, Hd = 600, 128, 512, 256  # 64 x 64 tiles for both layers
     f = lambda *s: rng.standard_normal(s).astype(np.float32)
     bf = lambda x: to_dev(wl.f32_to_bf16_bits(x))
     h, w1, w2 = bf(f(M, Hc)), bf(f(F, Hc) / math.sqrt(Hc)), bf(f(Hd, F) / math.sqrt(F))
