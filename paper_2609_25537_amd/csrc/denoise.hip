@@ -628,7 +628,7 @@ hipError_t launch_gram(const DenoiseParams &p, hipStream_t stream) {
 // 13.1 / 11.6 us, 12288 tokens 20.2 / 18.8 us (18432 tokens at g = 4 stay
 // whole: 28.8 us).
 template <typename T, int G>
-void launch_score(const DenoiseParams &p, hipStream_t stream) {
+hipError_t launch_score(const DenoiseParams &p, hipStream_t stream) {
     constexpr int kHalf = kTokensPerWave > 1 ? kTokensPerWave / 2 : 1;
     const bool few = (long long)p.B * p.n < 2048LL * kTokensPerWave;
     const int per_wg = 4 * (few ? kHalf : kTokensPerWave);
@@ -637,27 +637,27 @@ void launch_score(const DenoiseParams &p, hipStream_t stream) {
     const dim3 grid(gx, p.B);
     if (few) denoise_score_kernel<T, G, kHalf><<<grid, 256, 0, stream>>>(p);
     else denoise_score_kernel<T, G, kTokensPerWave><<<grid, 256, 0, stream>>>(p);
+    return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_scores(const DenoiseParams &p, hipStream_t stream) {
-    if (sizeof(T) == 2 && CMC_DENOISE_MFMA) {
+    if constexpr (sizeof(T) == 2 && CMC_DENOISE_MFMA) {
         switch (p.g) {
             case 1: return launch_gram<1>(p, stream);
             case 2: return launch_gram<2>(p, stream);
             case 3: return launch_gram<3>(p, stream);
             case 4: return launch_gram<4>(p, stream);
-            default: return hipErrorInvalidValue;
+        }
+    } else {
+        switch (p.g) {
+            case 1: return launch_score<T, 1>(p, stream);
+            case 2: return launch_score<T, 2>(p, stream);
+            case 3: return launch_score<T, 3>(p, stream);
+            case 4: return launch_score<T, 4>(p, stream);
         }
     }
-    switch (p.g) {
-        case 1: launch_score<T, 1>(p, stream); break;
-        case 2: launch_score<T, 2>(p, stream); break;
-        case 3: launch_score<T, 3>(p, stream); break;
-        case 4: launch_score<T, 4>(p, stream); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
