@@ -146,7 +146,7 @@ def _on_host(t):
 # stream as a raw handle, looked up at the first use (importing this module
 # does not import torch).  A decode step's launch takes about 9 us on the GPU
 # and 3 us in the HIP runtime, so what the wrappers do around it counts: the
-# per-call lookups and helper calls are kept out of them (12.0 -> 8.8 us for a
+# per-call lookups and helper calls are kept out of them (12.0 -> 8.2 us for a
 # batch-1 step).
 _torch = _device_index = _raw_stream = None
 

@@ -7,9 +7,10 @@
 // gemm_nt_kernel: C[M][N] = A[M][K] . B[N][K]^T on MFMA, bf16 operands, fp32
 // accumulation.  A workgroup of WGM x WGN waves computes a tile of WGM WTM x
 // WGN WTN, each wave WTM x WTN as 16 x 16 v_mfma_f32_16x16x32_bf16 tiles:
-// 256 x 256 from eight waves of 128 x 64 where N allows (one workgroup per
-// CU), else 128 x 128 from four waves of 64 x 64 (three per CU).  K advances
-// BK at a time through two LDS buffers, staged from global memory through
+// 256 x 256 from eight waves of 128 x 64 (one workgroup per CU) where N
+// allows and there are enough such tiles, 128 x 128 from four waves of 64 x 64
+// (three per CU), or 64 x 64 from four waves of 32 x 32 where there are too few
+// of those as well (see launch_gemm).  K advances BK at a time through two LDS buffers, staged from global memory through
 // register sets used in turn (two by default), so a slice's loads have the
 // MFMA work of the slices before it to land.  LDS rows are padded by 8 bf16
 // (80 or 144 bytes) so that the 16-byte fragment reads of 8 consecutive
@@ -20,8 +21,8 @@
 // and rounds to bf16 (the hidden activations, kept in the workspace); the
 // second layer's fp32 result goes to the output.
 //
-// bridge_norm_kernel: one wave per output row, in place, the row held in
-// registers: mean and biased variance (two passes over the registers),
+// bridge_norm_kernel, bridge_norm_wg_kernel: one wave per output row, or one
+// workgroup where the rows are few, in place, the row held in registers: mean and biased variance (two passes over the registers),
 // LayerNorm with gamma/beta, nu tanh, the row norm, and the cap.
 //
 // cme_norm_kernel (optional): |h_j| of every input row, the norms that
@@ -598,10 +599,11 @@ hipError_t launch_gemm_t(int epi, const GemmParams &g, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Build-time tuning knob: 1 runs N % 256 == 0 shapes on 256 x 256 tiles of
-// eight waves, 128 x 64 each (one workgroup per CU), with K slices of
-// CMC_BRIDGE_BIG_BK and CMC_BRIDGE_BIG_STAGES register stages; other shapes
-// (and 0) use 128 x 128 tiles of four 64 x 64 waves.  On the 49152 x 1280 ->
+// Build-time tuning knob: 1 runs N % 256 == 0 shapes with more than 192 tiles
+// of 256 x 256 on such tiles of eight waves, 128 x 64 each (one workgroup per
+// CU), with K slices of CMC_BRIDGE_BIG_BK and CMC_BRIDGE_BIG_STAGES register
+// stages; other shapes (and 0) use 128 x 128 tiles of four 64 x 64 waves, or 64
+// x 64 tiles of four 32 x 32 waves below 384 of those.  On the 49152 x 1280 ->
 // 4096 -> 4096 projection: 128 x 128 tiles 3.22 ms per call; 256 x 256 tiles
 // with 32-wide slices 3.14 ms (two stages) and 2.99 ms (three), with 64-wide
 // slices 3.05 ms (one stage) and 2.94 ms (two); the same with the transposed
