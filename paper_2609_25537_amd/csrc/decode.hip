@@ -358,24 +358,29 @@ struct QOperand<uint16_t, DH, G> {
 template <int DH, int G>
 struct QOperand<float, DH, G> {
     static constexpr int kChunks = DH / 16;
-    // One or two heads: the dot products on the VALU, the lane's chunks of
-    // every head in registers.  An fp32 MFMA step takes 32 cycles however few
-    // of its 16 rows are distinct heads: DH/4 of them per block against
-    // G (DH/4 + 6) VALU instructions of 4 cycles.
-    static constexpr bool kDot = G * DH <= 256 && G <= 2;
-    static constexpr bool kLds = !kDot && kQInLds<float, DH, G>;
+    // Few heads: the dot products on the VALU.  An fp32 MFMA step takes 32
+    // cycles however few of its 16 rows are distinct heads: DH/4 of them per
+    // block against G (DH/4 + 6) VALU instructions of 4 cycles.  One or two
+    // heads keep the lane's chunks of q in registers; two or four of 256 read
+    // them from LDS.  Four heads of 256, 24 pairs of 3072 keys: 45.1 us on
+    // MFMA, 44.7 so; 768 keys 22.3 / 22.5; 120 keys 17.5 / 18.7; output error
+    // against 64 bits 2.3e-7 / 1.7e-7 (the MFMA's one run of 16 chunks; shorter
+    // runs spilled 48 registers: 1.8e-7, 140 us at 104 pairs of 3072 keys
+    // against 134).  Two heads, 3072 keys of 64 pairs: 77 / 71.
+    static constexpr bool kLds = kQInLds<float, DH, G>;
+    static constexpr bool kDot = kLds ? G <= 4 : G * DH <= 256 && G <= 2;
     static constexpr int kLdsWords = kLds ? kChunks * 4 * G : 1;  // 16-byte words per wave
-    float4 x[kDot ? G * kChunks : kLds ? 1 : kChunks];
+    float4 x[kLds ? 1 : kDot ? G * kChunks : kChunks];
     uint4 *lds;
     bool ready;
     __device__ __forceinline__ void load(const DecodeParams &p, int b, int kvh) {
         const int lane = threadIdx.x & 63;
         const int r16 = lane & 15, q4 = lane >> 4;
         const float *q0 = p.q + ((size_t)b * p.Hq + (size_t)kvh * G) * DH + 4 * q4;
-        constexpr int kRows = kDot ? G : 1;
+        constexpr int kRows = kDot && !kLds ? G : 1;
 #pragma unroll
         for (int g = 0; g < kRows; ++g) {
-            const float *qp = q0 + (kDot ? g : r16 % G) * DH;
+            const float *qp = q0 + (kDot && !kLds ? g : r16 % G) * DH;
 #pragma unroll
             for (int i = 0; i < kChunks; ++i) {
                 const float4 t = *reinterpret_cast<const float4 *>(qp + 16 * i);
@@ -397,7 +402,9 @@ struct QOperand<float, DH, G> {
                 float d[4] = {0.f, 0.f, 0.f, 0.f};  // short chains: less rounding, more in flight
 #pragma unroll
                 for (int i = 0; i < kChunks; ++i) {
-                    const float4 a = x[g * kChunks + i];
+                    float4 a;
+                    if constexpr (kLds) a = __builtin_bit_cast(float4, lds[(i * 4 + (threadIdx.x & 63) / 16) * G + g]);
+                    else a = x[g * kChunks + i];
                     d[0] = fmaf(a.x, __uint_as_float(kr[i].x), d[0]);
                     d[1] = fmaf(a.y, __uint_as_float(kr[i].y), d[1]);
                     d[2] = fmaf(a.z, __uint_as_float(kr[i].z), d[2]);
@@ -416,29 +423,19 @@ struct QOperand<float, DH, G> {
             } else {
                 a = x[kDot ? 0 : i];
             }
-            // Short runs, so that no partial sum is rounded often, over two
-            // accumulators where the registers are short, else four.  Output
-            // error against 64 bits (140 pairs, 300 keys) with runs of four
-            // chunks, and one of 16 for four heads of 256 / now: Dh = 64, G =
-            // 4 1.66e-7 / 1.61e-7, G = 8 1.67e-7 / 1.60e-7; Dh = 128, G = 8
-            // 1.72e-7 / 1.66e-7; Dh = 256, G = 4 2.25e-7 / 1.83e-7 (the lane
-            // sums that this walk replaced: 1.52e-7, 1.52e-7, 1.63e-7,
-            // 1.75e-7).  Times are the same but for four heads of 256: 136
-            // pairs of 120 keys 24.4 / 28.1 us, 24 pairs of 768 keys 22.6 /
-            // 23.4, 184 pairs of 3072 keys 258 / 265.
-            constexpr bool kTwo = DH > 128 && G == 4;
-            constexpr int kRun = DH <= 128 || kTwo ? 2 : 4;
             c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, __uint_as_float(kr[i].x), c, 0, 0, 0);
             c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, __uint_as_float(kr[i].y), c1, 0, 0, 0);
-            if constexpr (kTwo) {
-                c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c, 0, 0, 0);
-                c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(kr[i].w), c1, 0, 0, 0);
-            } else {
-                c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c2, 0, 0, 0);
-                c3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(kr[i].w), c3, 0, 0, 0);
-            }
+            c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c2, 0, 0, 0);
+            c3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(kr[i].w), c3, 0, 0, 0);
+            // Short runs, so that no partial sum is rounded often.  Output
+            // error against 64 bits (140 pairs, 300 keys) with runs of four
+            // chunks / two: Dh = 64, G = 4 1.66e-7 / 1.61e-7, G = 8 1.67e-7 /
+            // 1.60e-7; Dh = 128, G = 8 1.72e-7 / 1.66e-7, at the same times
+            // (the lane sums that this walk replaced: 1.52e-7, 1.52e-7,
+            // 1.63e-7).  Dh = 256: 1.7e-7 with four.
+            constexpr int kRun = DH <= 128 ? 2 : 4;
             if (i % kRun == kRun - 1) {
-                sum = sum + (kTwo ? c + c1 : (c + c1) + (c2 + c3));
+                sum = sum + ((c + c1) + (c2 + c3));
                 c = c1 = c2 = c3 = floatx4{0.f, 0.f, 0.f, 0.f};
             }
         }
