@@ -566,8 +566,9 @@ __global__ __launch_bounds__(256) void cme_norm_kernel(const uint16_t *h, int M,
 hipError_t launch_norm(const BridgeParams &p, hipStream_t stream) {
     // A workgroup per row below 2048 rows (2048 waves fill the chip with one
     // row each).  Whole calls, Hc = 1280, F = Hd = 4096, wave / workgroup per
-    // row: 48 rows 47.3 / 39.5 us, 768 rows 89.3 / 85.5, 3072 rows 212.9 /
-    // 213.5, 16384 rows 884 / 899, 49152 rows 2539 / 2553.
+    // row: 48 rows 42.5 / 34.9 us, 768 rows 85.5 / 78.3, 2000 rows 139.5 /
+    // 133.9, 3072 rows 193.2 / 190.5, 16384 rows 835 / 839, 49152 rows 2480 /
+    // 2495.
     if (p.M < 2048 && p.Hd <= 1024 * 4) {
         if (p.Hd <= 1024) bridge_norm_wg_kernel<1><<<p.M, 256, 0, stream>>>(p);
         else if (p.Hd <= 2048) bridge_norm_wg_kernel<2><<<p.M, 256, 0, stream>>>(p);
