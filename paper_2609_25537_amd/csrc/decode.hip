@@ -23,7 +23,8 @@
 //     bf16 parts (hi + lo, two MFMAs per slice, for G <= 4; three parts, the
 //     whole fp32 significand, for G = 8), which keeps the logit error at the
 //     level of fp32 accumulation.
-//   fp32 K/V: v_mfma_f32_16x16x4_f32, fp32 products and sums throughout.
+//   fp32 K/V: v_mfma_f32_16x16x4_f32, or the VALU where the heads are few (see
+//     QOperand<float>), fp32 products and sums throughout.
 // P V runs on the VALU in fp32 in four quarters of 4 keys: lane l owns key
 // (l & 3) of each quarter and Dh/16 dims; the p values reach that layout
 // through 16 x G floats of LDS private to the wave.  V rows are loaded
@@ -39,9 +40,9 @@
 // trips, not a stream): the first K/V loads depend only on kernel arguments
 // that arrive preloaded in SGPRs.  The ring count is fetched with a vector
 // load and read where the masks need it, q is loaded and split after the
-// first K/V loads are issued, and when the key list is split anyway the rows
-// appended in this call get a split of their own, so no workgroup runs two
-// dependent phases.  Measured, the step is bound by that chain and by memory:
+// first K/V loads are issued, and where the key list is split often enough
+// the rows appended in this call get a split of their own, so no workgroup runs
+// two dependent phases (see plan_decode).  Measured, the step is bound by that chain and by memory:
 // with P V taken out entirely a step got only 2-3% faster.
 //
 // Split merge, inside the same launch: with S == 1 the workgroup writes the
@@ -87,8 +88,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // next block's prefetch.
 __device__ __forceinline__ void wave_lds_sync() { asm volatile("" ::: "memory"); }
 
-// 2^x with the hardware instruction alone (no denormal-result fix-up; a
-// softmax weight below 2^-126 contributes nothing at fp32 precision anyway).
+// 2^x with the hardware instruction alone: results below 2^-126 are 0 (see
+// kSmallWeights; the waves' and splits' weights at the merge always take it).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Whether softmax weights below 2^-126 are kept (as the library's exp2f gives
