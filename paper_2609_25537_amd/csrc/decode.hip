@@ -92,6 +92,38 @@ __device__ __forceinline__ void wave_lds_sync() { asm volatile("" ::: "memory");
 // kSmallWeights; the waves' and splits' weights at the merge always take it).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// d[e] += q[e] of lane I .. I + 3 of this lane's 16-lane row times element e of
+// k0 .. k3, in that order, each a multiply-add with a DPP row broadcast (the
+// compiler makes a move and a multiply-add of it).  The s_nop covers the two
+// wait states between a VALU write of q and its DPP read, which the compiler
+// cannot see in here.
+template <int I>
+__device__ __forceinline__ void row_fma(float (&d)[4], const float4 &q, const uint4 &k0, const uint4 &k1, const uint4 &k2,
+                                        const uint4 &k3) {
+    asm("s_nop 1\n"
+        "v_fmac_f32_dpp %[d0], %[q0], %[a0] row_newbcast:%[i0] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d1], %[q1], %[a1] row_newbcast:%[i0] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d2], %[q2], %[a2] row_newbcast:%[i0] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d3], %[q3], %[a3] row_newbcast:%[i0] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d0], %[q0], %[b0] row_newbcast:%[i1] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d1], %[q1], %[b1] row_newbcast:%[i1] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d2], %[q2], %[b2] row_newbcast:%[i1] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d3], %[q3], %[b3] row_newbcast:%[i1] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d0], %[q0], %[c0] row_newbcast:%[i2] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d1], %[q1], %[c1] row_newbcast:%[i2] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d2], %[q2], %[c2] row_newbcast:%[i2] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d3], %[q3], %[c3] row_newbcast:%[i2] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d0], %[q0], %[e0] row_newbcast:%[i3] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d1], %[q1], %[e1] row_newbcast:%[i3] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d2], %[q2], %[e2] row_newbcast:%[i3] row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %[d3], %[q3], %[e3] row_newbcast:%[i3] row_mask:0xf bank_mask:0xf"
+        : [d0] "+&v"(d[0]), [d1] "+&v"(d[1]), [d2] "+&v"(d[2]), [d3] "+&v"(d[3])
+        : [q0] "v"(q.x), [q1] "v"(q.y), [q2] "v"(q.z), [q3] "v"(q.w), [a0] "v"(k0.x), [a1] "v"(k0.y), [a2] "v"(k0.z),
+          [a3] "v"(k0.w), [b0] "v"(k1.x), [b1] "v"(k1.y), [b2] "v"(k1.z), [b3] "v"(k1.w), [c0] "v"(k2.x), [c1] "v"(k2.y),
+          [c2] "v"(k2.z), [c3] "v"(k2.w), [e0] "v"(k3.x), [e1] "v"(k3.y), [e2] "v"(k3.z), [e3] "v"(k3.w), [i0] "n"(I),
+          [i1] "n"(I + 1), [i2] "n"(I + 2), [i3] "n"(I + 3));
+}
+
 // Whether softmax weights below 2^-126 are kept (as the library's exp2f gives
 // them; times a large value they count) instead of taken as 0.  A lane that
 // holds one takes a branch.  24 ragged sequences of 64/8 heads 35.1 -> 35.8
@@ -264,11 +296,11 @@ struct NewRows {
 //
 // Where the operand would take the registers that a second wave per SIMD
 // needs (eight heads of bf16: three parts and 8 DH/16 accumulators per lane;
-// several 256-wide fp32 heads), the wave keeps it in LDS of its own instead
+// eight 256-wide fp32 heads), the wave keeps it in LDS of its own instead
 // and reads it back for every block: 16 bytes per lane and MFMA (bf16) or
 // four MFMAs (fp32), one copy per head.
 template <typename T, int DH, int G>
-constexpr bool kQInLds = sizeof(T) == 2 ? G > 4 : DH > 128 && G > 1;
+constexpr bool kQInLds = sizeof(T) == 2 ? G > 4 : DH > 128 && G > 4;
 
 template <typename T, int DH, int G>
 struct QOperand;
@@ -362,34 +394,39 @@ struct QOperand<float, DH, G> {
     // Few heads: the dot products on the VALU.  An fp32 MFMA step takes 32
     // cycles however few of its 16 rows are distinct heads: DH/4 of them per
     // block against G (DH/4 + 6) VALU instructions of 4 cycles.  One or two
-    // heads keep the lane's chunks of q in registers; two or four of 256 read
-    // them from LDS.  Four heads of 256, 24 pairs of 3072 keys: 45.1 us on
-    // MFMA, 44.7 so; 768 keys 22.3 / 22.5; 120 keys 17.5 / 18.7; output error
-    // against 64 bits 2.3e-7 / 1.7e-7 (the MFMA's one run of 16 chunks; shorter
-    // runs spilled 48 registers: 1.8e-7, 140 us at 104 pairs of 3072 keys
-    // against 134).  Two heads, 3072 keys of 64 pairs: 77 / 71.
+    // heads keep the lane's chunks of q in registers.  Two or four of 256 keep
+    // chunk i of every head in lane i of each 16-lane row, and the multiply
+    // takes it from there (a DPP row broadcast): G registers instead of LDS
+    // reads, whose 64 per block and wave took as long as the products.  Four
+    // heads of 256, MFMA in one run of 16 chunks / q read from LDS / so: 24
+    // pairs of 768 keys 22.4 / 22.5 / 19.4 us, 136 of 120 keys 23.1 / 27.0 /
+    // 20.6, 184 of 3072 keys 244 / 248 / 202; output error against 64 bits
+    // 2.3e-7 / 1.7e-7 / 1.7e-7 (shorter MFMA runs spilled 48 registers).  Two
+    // heads, 24 pairs of 768 keys 19.0 / 18.0 / 15.7.
+    static constexpr bool kRow = DH == 256 && (G == 2 || G == 4);
+    static constexpr bool kDot = kRow || (G * DH <= 256 && G <= 2);
     static constexpr bool kLds = kQInLds<float, DH, G>;
-    static constexpr bool kDot = kLds ? G <= 4 : G * DH <= 256 && G <= 2;
     static constexpr int kLdsWords = kLds ? kChunks * 4 * G : 1;  // 16-byte words per wave
-    float4 x[kLds ? 1 : kDot ? G * kChunks : kChunks];
+    float4 x[kRow ? G : kDot ? G * kChunks : kLds ? 1 : kChunks];
     uint4 *lds;
     bool ready;
     __device__ __forceinline__ void load(const DecodeParams &p, int b, int kvh) {
         const int lane = threadIdx.x & 63;
         const int r16 = lane & 15, q4 = lane >> 4;
         const float *q0 = p.q + ((size_t)b * p.Hq + (size_t)kvh * G) * DH + 4 * q4;
-        constexpr int kRows = kDot && !kLds ? G : 1;
+        constexpr int kRows = kDot ? G : 1;
+        constexpr int kLoads = kRow ? 1 : kChunks;
 #pragma unroll
         for (int g = 0; g < kRows; ++g) {
-            const float *qp = q0 + (kDot && !kLds ? g : r16 % G) * DH;
+            const float *qp = q0 + (kDot ? g : r16 % G) * DH + (kRow ? 16 * r16 : 0);
 #pragma unroll
-            for (int i = 0; i < kChunks; ++i) {
+            for (int i = 0; i < kLoads; ++i) {
                 const float4 t = *reinterpret_cast<const float4 *>(qp + 16 * i);
                 const float4 u = make_float4(t.x * p.qscale, t.y * p.qscale, t.z * p.qscale, t.w * p.qscale);
                 if constexpr (kLds) {
                     if (r16 < G) lds[(i * 4 + q4) * G + r16] = __builtin_bit_cast(uint4, u);
                 } else {
-                    x[g * kChunks + i] = u;
+                    x[g * kLoads + i] = u;
                 }
             }
         }
@@ -401,15 +438,21 @@ struct QOperand<float, DH, G> {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float d[4] = {0.f, 0.f, 0.f, 0.f};  // short chains: less rounding, more in flight
+                if constexpr (kRow) {
+                    static_assert(!kRow || kChunks == 16, "a chunk per lane of a row");
+                    row_fma<0>(d, x[g], kr[0], kr[1], kr[2], kr[3]);
+                    row_fma<4>(d, x[g], kr[4], kr[5], kr[6], kr[7]);
+                    row_fma<8>(d, x[g], kr[8], kr[9], kr[10], kr[11]);
+                    row_fma<12>(d, x[g], kr[12], kr[13], kr[14], kr[15]);
+                } else {
 #pragma unroll
-                for (int i = 0; i < kChunks; ++i) {
-                    float4 a;
-                    if constexpr (kLds) a = __builtin_bit_cast(float4, lds[(i * 4 + (threadIdx.x & 63) / 16) * G + g]);
-                    else a = x[g * kChunks + i];
-                    d[0] = fmaf(a.x, __uint_as_float(kr[i].x), d[0]);
-                    d[1] = fmaf(a.y, __uint_as_float(kr[i].y), d[1]);
-                    d[2] = fmaf(a.z, __uint_as_float(kr[i].z), d[2]);
-                    d[3] = fmaf(a.w, __uint_as_float(kr[i].w), d[3]);
+                    for (int i = 0; i < kChunks; ++i) {
+                        const float4 a = x[g * kChunks + i];
+                        d[0] = fmaf(a.x, __uint_as_float(kr[i].x), d[0]);
+                        d[1] = fmaf(a.y, __uint_as_float(kr[i].y), d[1]);
+                        d[2] = fmaf(a.z, __uint_as_float(kr[i].z), d[2]);
+                        d[3] = fmaf(a.w, __uint_as_float(kr[i].w), d[3]);
+                    }
                 }
                 c[g] = lane_reduce<OpSum, 16, kWave>((d[0] + d[1]) + (d[2] + d[3]));
             }
