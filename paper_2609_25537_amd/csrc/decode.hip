@@ -294,21 +294,17 @@ struct NewRows {
 // 16-byte chunks 4 i + lane / 16 of the row; the dims of a chunk are the k
 // indices of one MFMA (bf16) or of four (fp32), in the same order for q.
 //
-// Where the operand would take the registers that a second wave per SIMD
-// needs (eight heads of bf16: three parts and 8 DH/16 accumulators per lane;
-// eight 256-wide fp32 heads), the wave keeps it in LDS of its own instead
-// and reads it back for every block: 16 bytes per lane and MFMA (bf16) or
-// four MFMAs (fp32), one copy per head.
-template <typename T, int DH, int G>
-constexpr bool kQInLds = sizeof(T) == 2 ? G > 4 : DH > 128 && G > 4;
-
+// Eight heads of bf16 (three parts, beside 8 DH/16 accumulators per lane)
+// keep the operand in LDS of the wave's own instead, where its registers would
+// cost the second wave per SIMD, and read it back for every block: 16 bytes per
+// lane and MFMA, one copy per head.
 template <typename T, int DH, int G>
 struct QOperand;
 
 template <int DH, int G>
 struct QOperand<uint16_t, DH, G> {
     static constexpr int kChunks = DH / 32;
-    static constexpr bool kLds = kQInLds<uint16_t, DH, G>;
+    static constexpr bool kLds = G > 4;
     // bf16 parts of q: hi + lo carry 16 bits of its significand; the third
     // completes fp32's 24.  (Two parts: output error 2.6e-6 against 64 bits;
     // three: 2e-7, what an fp32 dot product gives.)
@@ -391,23 +387,24 @@ struct QOperand<uint16_t, DH, G> {
 template <int DH, int G>
 struct QOperand<float, DH, G> {
     static constexpr int kChunks = DH / 16;
-    // Few heads: the dot products on the VALU.  An fp32 MFMA step takes 32
-    // cycles however few of its 16 rows are distinct heads: DH/4 of them per
-    // block against G (DH/4 + 6) VALU instructions of 4 cycles.  One or two
-    // heads keep the lane's chunks of q in registers.  Two or four of 256 keep
-    // chunk i of every head in lane i of each 16-lane row, and the multiply
-    // takes it from there (a DPP row broadcast): G registers instead of LDS
-    // reads, whose 64 per block and wave took as long as the products.  Four
-    // heads of 256, MFMA in one run of 16 chunks / q read from LDS / so: 24
-    // pairs of 768 keys 22.4 / 22.5 / 19.4 us, 136 of 120 keys 23.1 / 27.0 /
-    // 20.6, 184 of 3072 keys 244 / 248 / 202; output error against 64 bits
-    // 2.3e-7 / 1.7e-7 / 1.7e-7 (shorter MFMA runs spilled 48 registers).  Two
-    // heads, 24 pairs of 768 keys 19.0 / 18.0 / 15.7.
-    static constexpr bool kRow = DH == 256 && (G == 2 || G == 4);
+    // Few heads, and rows of 256: the dot products on the VALU.  An fp32 MFMA
+    // step takes 32 cycles however few of its 16 rows are distinct heads: DH/4
+    // of them per block against G (DH/4 + 6) VALU instructions of 4 cycles.
+    // One or two heads keep the lane's chunks of q in registers.  Two to eight
+    // of 256 keep chunk i of every head in lane i of each 16-lane row, and the
+    // multiply takes it from there (a DPP row broadcast): G registers of four
+    // floats instead of LDS reads, whose 16 G per block and wave took as long
+    // as the products.  Four heads of 256, MFMA in one run of 16 chunks / q
+    // read from LDS / so: 24 pairs of 768 keys 22.4 / 22.5 / 19.4 us, 136 of
+    // 120 keys 23.1 / 27.0 / 20.6, 184 of 3072 keys 244 / 248 / 202; output
+    // error against 64 bits 2.3e-7 / 1.7e-7 / 1.7e-7 (shorter MFMA runs spilled
+    // 48 registers).  Eight heads, MFMA / so: 104 pairs of 3072 keys 159 / 137,
+    // 264 pairs of 120 keys 59 / 54.  Two heads, q from LDS / so: 24 pairs of
+    // 768 keys 18.0 / 15.7.
+    static constexpr bool kRow = DH == 256 && G >= 2;
     static constexpr bool kDot = kRow || (G * DH <= 256 && G <= 2);
-    static constexpr bool kLds = kQInLds<float, DH, G>;
-    static constexpr int kLdsWords = kLds ? kChunks * 4 * G : 1;  // 16-byte words per wave
-    float4 x[kRow ? G : kDot ? G * kChunks : kLds ? 1 : kChunks];
+    static constexpr int kLdsWords = 1;  // none needed
+    float4 x[kRow ? G : kDot ? G * kChunks : kChunks];
     uint4 *lds;
     bool ready;
     __device__ __forceinline__ void load(const DecodeParams &p, int b, int kvh) {
@@ -423,14 +420,9 @@ struct QOperand<float, DH, G> {
             for (int i = 0; i < kLoads; ++i) {
                 const float4 t = *reinterpret_cast<const float4 *>(qp + 16 * i);
                 const float4 u = make_float4(t.x * p.qscale, t.y * p.qscale, t.z * p.qscale, t.w * p.qscale);
-                if constexpr (kLds) {
-                    if (r16 < G) lds[(i * 4 + q4) * G + r16] = __builtin_bit_cast(uint4, u);
-                } else {
-                    x[g * kLoads + i] = u;
-                }
+                x[g * kLoads + i] = u;
             }
         }
-        if constexpr (kLds) wave_lds_sync();
     }
     __device__ __forceinline__ floatx4 scores(const uint4 (&kr)[kChunks]) const {
         floatx4 c = {0.f, 0.f, 0.f, 0.f}, c1 = c, c2 = c, c3 = c, sum = c;
@@ -454,19 +446,19 @@ struct QOperand<float, DH, G> {
                         d[3] = fmaf(a.w, __uint_as_float(kr[i].w), d[3]);
                     }
                 }
-                c[g] = lane_reduce<OpSum, 16, kWave>((d[0] + d[1]) + (d[2] + d[3]));
+                const float t = lane_reduce<OpSum, 16, kWave>((d[0] + d[1]) + (d[2] + d[3]));
+                if constexpr (G > 4) {  // the odd lane rows hold heads 4 .. 7
+                    const bool mine = (g >= 4) == (((threadIdx.x & 63) / 16) % 2 != 0);
+                    c[g % 4] = mine ? t : c[g % 4];
+                } else {
+                    c[g] = t;
+                }
             }
             return c;
         }
 #pragma unroll
         for (int i = 0; i < kChunks; ++i) {
-            float4 a;
-            if constexpr (kLds) {
-                const int lane = threadIdx.x & 63;
-                a = __builtin_bit_cast(float4, lds[(i * 4 + lane / 16) * G + lane % G]);
-            } else {
-                a = x[kDot ? 0 : i];
-            }
+            const float4 a = x[kDot ? 0 : i];
             c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, __uint_as_float(kr[i].x), c, 0, 0, 0);
             c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, __uint_as_float(kr[i].y), c1, 0, 0, 0);
             c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(kr[i].z), c2, 0, 0, 0);
@@ -476,8 +468,8 @@ struct QOperand<float, DH, G> {
             // chunks / two: Dh = 64, G = 4 1.66e-7 / 1.61e-7, G = 8 1.67e-7 /
             // 1.60e-7; Dh = 128, G = 8 1.72e-7 / 1.66e-7, at the same times
             // (the lane sums that this walk replaced: 1.52e-7, 1.52e-7,
-            // 1.63e-7).  Dh = 256: 1.7e-7 with four.
-            constexpr int kRun = DH <= 128 ? 2 : 4;
+            // 1.63e-7).
+            constexpr int kRun = 2;
             if (i % kRun == kRun - 1) {
                 sum = sum + ((c + c1) + (c2 + c3));
                 c = c1 = c2 = c3 = floatx4{0.f, 0.f, 0.f, 0.f};
