@@ -96,7 +96,8 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // k0 .. k3, in that order, each a multiply-add with a DPP row broadcast (the
 // compiler makes a move and a multiply-add of it).  The s_nop covers the two
 // wait states between a VALU write of q and its DPP read, which the compiler
-// cannot see in here.
+// cannot see in here.  (The five after a VALU write of EXEC are not needed:
+// EXEC is written by the scalar unit alone.)  All lanes must be active.
 template <int I>
 __device__ __forceinline__ void row_fma(float (&d)[4], const float4 &q, const uint4 &k0, const uint4 &k1, const uint4 &k2,
                                         const uint4 &k3) {
@@ -397,10 +398,10 @@ struct QOperand<float, DH, G> {
     // as the products.  Four heads of 256, MFMA in one run of 16 chunks / q
     // read from LDS / so: 24 pairs of 768 keys 22.4 / 22.5 / 19.4 us, 136 of
     // 120 keys 23.1 / 27.0 / 20.6, 184 of 3072 keys 244 / 248 / 202; output
-    // error against 64 bits 2.3e-7 / 1.7e-7 / 1.7e-7 (shorter MFMA runs spilled
-    // 48 registers).  Eight heads, MFMA / so: 104 pairs of 3072 keys 159 / 137,
-    // 264 pairs of 120 keys 59 / 54.  Two heads, q from LDS / so: 24 pairs of
-    // 768 keys 18.0 / 15.7.
+    // error against 64 bits 2.3e-7 / 1.7e-7 / 1.7e-7 (13 registers spill so, 48
+    // did with shorter MFMA runs).  Eight heads, MFMA / so: 104 pairs of 3072
+    // keys 159 / 137, 264 pairs of 120 keys 59 / 54.  Two heads, q from LDS /
+    // so: 24 pairs of 768 keys 18.0 / 15.7.
     static constexpr bool kRow = DH == 256 && G >= 2;
     static constexpr bool kDot = kRow || (G * DH <= 256 && G <= 2);
     static constexpr int kLdsWords = 1;  // none needed
